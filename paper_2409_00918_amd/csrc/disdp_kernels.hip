@@ -91,6 +91,22 @@ __device__ __forceinline__ uint32_t to_bf16(float x)
     return (u & 0x7fffffffu) > 0x7f800000u ? qnan : rounded;
 }
 
+// Four floats -> bf16 as to_bf16, two per register.  The hardware conversion
+// (two floats an instruction) rounds to nearest even and keeps denormals as
+// to_bf16 does; only its NaNs differ (they keep payload bits).
+__device__ __forceinline__ u32x2 to_bf16x4(const float (&p)[4])
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 lo = __builtin_convertvector((f32x2{p[0], p[1]}), bf16x2);
+    const bf16x2 hi = __builtin_convertvector((f32x2{p[2], p[3]}), bf16x2);
+    u32x2 w = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+    if (__builtin_expect(__builtin_isunordered(p[0], p[1]) || __builtin_isunordered(p[2], p[3]),
+                         0))
+        w = u32x2{to_bf16(p[0]) | (to_bf16(p[1]) << 16), to_bf16(p[2]) | (to_bf16(p[3]) << 16)};
+    return w;
+}
+
 // Contribution -> int32 at scale 2^k: exact scaling, rint (ties to even),
 // saturation, NaN -> 0 (the integer switch format, Section III-B), in three
 // instructions and no branches.
@@ -113,16 +129,29 @@ __device__ __forceinline__ int32_t saturate32(int64_t s)
 }
 
 // The step constants of a launch: by value in the arguments, or read from
-// memory when the kernel runs (one uniform load per wave, scalar cache).
+// memory when the kernel runs; either way by scalar loads (the constant
+// address space) issued while the contributions are in flight.  Left to
+// itself the compiler selects between the two addresses first, and each wave
+// then waits for one more round trip to memory after its contributions have
+// arrived; the empty asm keeps the reads under the (uniform) branch.
 template <class A>
 __device__ __forceinline__ StepScalars step_scalars_of(const A &a)
 {
-    return a.s_dev ? *a.s_dev : a.s;
+    StepScalars s = a.s;
+    if (a.s_dev) {
+        typedef const __attribute__((address_space(4))) float *ConstFloats;
+        const ConstFloats c = (ConstFloats)(uintptr_t)a.s_dev;
+        s = StepScalars{c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7], c[8], c[9]};
+        asm volatile("" : "+s"(s.b1), "+s"(s.omb1), "+s"(s.b2), "+s"(s.omb2), "+s"(s.bc1),
+                          "+s"(s.bc2), "+s"(s.decay), "+s"(s.lr), "+s"(s.eps),
+                          "+s"(s.grad_scale));
+    }
+    return s;
 }
 
 // One AdamW step on one element (decoupled decay, bias-corrected moments,
-// eps outside the square root).  `/` and sqrtf are the correctly rounded
-// IEEE operations on this target.
+// eps outside the square root), in the compiler's correctly rounded division
+// and square root, for any values.
 __device__ __forceinline__ void adamw(const StepScalars &s, float agg, float &p, float &m,
                                       float &v)
 {
@@ -135,6 +164,107 @@ __device__ __forceinline__ void adamw(const StepScalars &s, float agg, float &p,
     p = p * s.decay - s.lr * (mh / d);
     m = mi;
     v = vi;
+}
+
+// What a lane derives from the step constants while its loads are in
+// flight, for the short forms of the two divisions by a bias correction c:
+// zh = 1/c correctly rounded and zl = 1/c - zh.  `tame`: the constants lie
+// where those forms hold (see adamw4).
+struct Reciprocals {
+    float zh1, zl1, zh2, zl2;
+    bool tame;
+};
+
+__device__ __forceinline__ Reciprocals reciprocals(const StepScalars &s)
+{
+    Reciprocals r;
+    r.zh1 = 1.0f / s.bc1;
+    r.zl1 = __builtin_fmaf(-s.bc1, r.zh1, 1.0f) * r.zh1;
+    r.zh2 = 1.0f / s.bc2;
+    r.zl2 = __builtin_fmaf(-s.bc2, r.zh2, 1.0f) * r.zh2;
+    // not sunk to their use behind the waits for the loads
+    asm volatile("" : "+v"(r.zh1), "+v"(r.zl1), "+v"(r.zh2), "+v"(r.zl2));
+    // as integers (scalar compares): a sign bit or a NaN is above the ends
+    constexpr uint32_t kLo = (127u - 24u) << 23, kOne = 127u << 23, kEps = (127u + 40u) << 23;
+    r.tame = __float_as_uint(s.bc1) - kLo <= kOne - kLo &&
+             __float_as_uint(s.bc2) - kLo <= kOne - kLo && __float_as_uint(s.eps) <= kEps;
+    return r;
+}
+
+// x / c, correctly rounded, for 2^-24 <= c <= 1 and 2^-96 <= |x| <= 2^60.
+// q is x * (1/c) with 1/c held in two floats, so within 0.5 + 2^-21 units of
+// the quotient; the remainder x - q*c is then exact, and as zh is the
+// correctly rounded 1/c one more step rounds correctly (Markstein, "Computation
+// of elementary functions on the IBM RISC System/6000 processor", 1990).
+__device__ __forceinline__ float div_const(float x, float c, float zh, float zl)
+{
+    const float q = __builtin_fmaf(x, zh, x * zl);
+    return __builtin_fmaf(__builtin_fmaf(-q, c, x), zh, q);
+}
+
+// sqrt(x), correctly rounded on gfx950 for 2^-100 <= x <= 2^100: one
+// correction of x * v_rsq_f32(x).  Every float of that range was compared
+// with sqrtf on MI355X (rsq is a function of the significand and the
+// exponent's parity, so that is 2^24 cases, each at every scale).
+__device__ __forceinline__ float sqrt_mid(float x)
+{
+    const float y = __builtin_amdgcn_rsqf(x);
+    const float g = x * y;
+    return __builtin_fmaf(__builtin_fmaf(-g, g, x), 0.5f * y, g);
+}
+
+// n / d as the compiler's correctly rounded division computes it where no
+// operand needs scaling: 2^-60 <= |n| <= 2^44, 2^-48 <= d <= 2^46.
+__device__ __forceinline__ float div_mid(float n, float d)
+{
+    float y = __builtin_amdgcn_rcpf(d);
+    y = __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
+    float q = n * y;
+    q = __builtin_fmaf(__builtin_fmaf(-d, q, n), y, q);
+    return __builtin_fmaf(__builtin_fmaf(-d, q, n), y, q);
+}
+
+// adamw on the four elements of a lane, the same bits in about half the
+// instructions (372 -> 226 vector instructions for the W = 8 fp32 group).
+// The kernel is bound by memory at shard sizes, but a launch of a few
+// megabytes runs its waves in step -- all load, all compute, all store -- and
+// the arithmetic adds to its time.  The short divisions and square root need
+// the moments in a middle range (2^-60..2^20 for |m|, 2^-96..2^60 for v),
+// which gradients of trained models keep; a lane with an element outside it
+// (a zero, denormal, infinity or NaN included) takes the general form.
+__device__ __forceinline__ void adamw4(const StepScalars &s, const Reciprocals &r,
+                                       const float (&agg)[4], float (&p)[4], float (&m)[4],
+                                       float (&v)[4])
+{
+    constexpr uint32_t kMLo = (127u - 60u) << 23, kMHi = (127u + 20u) << 23;
+    constexpr uint32_t kVLo = (127u - 96u) << 23, kVHi = (127u + 60u) << 23;
+    float mi[4], vi[4];
+    uint32_t far_m = 0, far_v = 0;   // largest distance above the lower ends (wraps below them)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float g = agg[e] * s.grad_scale;
+        mi[e] = s.b1 * m[e] + s.omb1 * g;
+        vi[e] = s.b2 * v[e] + s.omb2 * (g * g);
+        const uint32_t dm = (__float_as_uint(mi[e]) << 1) - 2 * kMLo;
+        const uint32_t dv = __float_as_uint(vi[e]) - kVLo;
+        far_m = dm > far_m ? dm : far_m;
+        far_v = dv > far_v ? dv : far_v;
+    }
+    if (__builtin_expect(r.tame && far_m <= 2 * (kMHi - kMLo) && far_v <= kVHi - kVLo, 1)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float mh = div_const(mi[e], s.bc1, r.zh1, r.zl1);
+            const float vh = div_const(vi[e], s.bc2, r.zh2, r.zl2);
+            const float d = sqrt_mid(vh) + s.eps;
+            p[e] = p[e] * s.decay - s.lr * div_mid(mh, d);
+            m[e] = mi[e];
+            v[e] = vi[e];
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            adamw(s, agg[e], p[e], m[e], v[e]);
+    }
 }
 
 // ---- loading contributions -----------------------------------------------
@@ -236,7 +366,8 @@ struct Acc {
 
 template <int MODE, bool ADAM, class A>
 __device__ __forceinline__ void finish_group(const A &a, int64_t grp, const float (&agg)[4],
-                                             const int32_t (&ai)[4], f32x4 P, f32x4 M, f32x4 V)
+                                             const int32_t (&ai)[4], f32x4 P, f32x4 M, f32x4 V,
+                                             const StepScalars &sc, const Reciprocals &rc)
 {
     if (a.agg_f32)
         st_nt(reinterpret_cast<f32x4 *>(a.agg_f32) + grp, f32x4{agg[0], agg[1], agg[2], agg[3]});
@@ -248,17 +379,12 @@ __device__ __forceinline__ void finish_group(const A &a, int64_t grp, const floa
         float p[4] = {P.x, P.y, P.z, P.w};
         float m[4] = {M.x, M.y, M.z, M.w};
         float v[4] = {V.x, V.y, V.z, V.w};
-        const StepScalars sc = step_scalars_of(a);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            adamw(sc, agg[e], p[e], m[e], v[e]);
+        adamw4(sc, rc, agg, p, m, v);
         st_nt(reinterpret_cast<f32x4 *>(a.p) + grp, f32x4{p[0], p[1], p[2], p[3]});
         st_nt(reinterpret_cast<f32x4 *>(a.m) + grp, f32x4{m[0], m[1], m[2], m[3]});
         st_nt(reinterpret_cast<f32x4 *>(a.v) + grp, f32x4{v[0], v[1], v[2], v[3]});
         if (a.p16)
-            st_nt(reinterpret_cast<u32x2 *>(a.p16) + grp,
-                  u32x2{to_bf16(p[0]) | (to_bf16(p[1]) << 16),
-                        to_bf16(p[2]) | (to_bf16(p[3]) << 16)});
+            st_nt(reinterpret_cast<u32x2 *>(a.p16) + grp, to_bf16x4(p));
     }
 }
 
@@ -270,6 +396,8 @@ __device__ __forceinline__ void process_group(const A &a, int64_t grp)
 {
     typename Contrib<GT>::type c[W][4];
     f32x4 P{}, M{}, V{};
+    StepScalars sc;
+    Reciprocals rc;
 #pragma unroll
     for (int w = 0; w < W; ++w)
         load_group<GT>(a.g[w], grp, c[w]);
@@ -277,6 +405,8 @@ __device__ __forceinline__ void process_group(const A &a, int64_t grp)
         P = ld_nt(reinterpret_cast<const f32x4 *>(a.p) + grp);
         M = ld_nt(reinterpret_cast<const f32x4 *>(a.m) + grp);
         V = ld_nt(reinterpret_cast<const f32x4 *>(a.v) + grp);
+        sc = step_scalars_of(a);
+        rc = reciprocals(sc);
     }
     float agg[4];
     int32_t ai[4];
@@ -289,7 +419,7 @@ __device__ __forceinline__ void process_group(const A &a, int64_t grp)
             acc.next(c[w][e], a.qscale);
         agg[e] = acc.result(a.dqscale, ai[e]);
     }
-    finish_group<MODE, ADAM>(a, grp, agg, ai, P, M, V);
+    finish_group<MODE, ADAM>(a, grp, agg, ai, P, M, V, sc, rc);
 }
 
 // ---- one group per lane, W known only at run time (W <= 64) ---------------
@@ -325,10 +455,14 @@ __device__ __forceinline__ void process_group_rt(const A &a, int64_t grp)
 {
     constexpr int kChunk = GT == kGradBF16 ? 16 : 8;
     f32x4 P{}, M{}, V{};
+    StepScalars sc;
+    Reciprocals rc;
     if constexpr (ADAM) {
         P = ld_nt(reinterpret_cast<const f32x4 *>(a.p) + grp);
         M = ld_nt(reinterpret_cast<const f32x4 *>(a.m) + grp);
         V = ld_nt(reinterpret_cast<const f32x4 *>(a.v) + grp);
+        sc = step_scalars_of(a);
+        rc = reciprocals(sc);
     }
     Acc<MODE> acc[4];
     int w0 = 0;
@@ -356,7 +490,7 @@ __device__ __forceinline__ void process_group_rt(const A &a, int64_t grp)
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         agg[e] = acc[e].result(a.dqscale, ai[e]);
-    finish_group<MODE, ADAM>(a, grp, agg, ai, P, M, V);
+    finish_group<MODE, ADAM>(a, grp, agg, ai, P, M, V, sc, rc);
 }
 
 // ---- one element -----------------------------------------------------------
@@ -537,32 +671,35 @@ __global__ DISDP_WAVE_LAUNCH_BOUNDS void quantize_element_kernel(QuantizeArgs q)
 
 // ---- host side: grid sizing and dispatch --------------------------------------
 
-// Resident waves per CU for a fixed-point kernel converting float
-// contributions, by the bytes of loads a lane keeps in flight, as in fp32
-// mode; a lane converting bf16 contributions (twice the conversions per
-// byte) holds its loads for a smaller share of the time and wants more
-// waves.  Interleaved A/B of the fused call at n = 4e8 over caps of 6-14
-// (TB/s at the chosen cap, the next best in brackets): fp32 W = 1, 2
-// (64, 80 B) 14: 6.48, 6.49 (12: 6.28, 6.41); W = 4 (112 B) 12: 6.61;
-// W = 8 (176 B) 8: 6.59 (10: 6.49); W = 12, 24 (240, 432 B) 6: 6.44, 6.04
-// (8: 6.24, 6.01); bf16 W = 4 (80 B) 14: 6.43 (12: 6.28); W = 8 (112 B)
-// 12: 6.38 (14: 6.34); W = 16, 32 (176, 304 B) 10: 6.19, 6.00 (8: 6.16,
-// 5.93).  Int32 contributions need no conversion and take the fp32-mode
-// caps.
-constexpr int fixed_mode_waves(int lane_bytes, bool bf16)
+// Resident waves per CU of the fused kernels, by the bytes of loads a lane
+// keeps in flight (4 elements of each contribution, p, m and v).  What
+// streams best is the fewest waves that still cover the memory's latency: the
+// tiles in flight are then the shortest stretch of every array, and one wave
+// more per CU costs up to 3%, one fewer up to 10%.  Interleaved over caps of
+// 4-14 at n = 2e8, TB/s at the chosen cap (one fewer; one more): fp32 W = 1
+// (64 B) 9: 6.75 (6.71; 6.69); W = 2 (80 B) 8: 6.76 (6.66; 6.69); W = 4 (112
+// B) 7: 6.79 (6.78; 6.70); W = 6 (144 B) 6: 6.77 (6.77; 6.65); W = 8 (176 B)
+// 5: 6.64 (6.56; 6.41); W = 12, 16 (240, 304 B) 4: 6.49, 6.38 (5: 6.33,
+// 6.28); bf16 W = 4, 8, 12, 16: 6.70, 6.62, 6.59, 6.46 at 8, 7, 6, 5.
+// Fixed point converting fp32 is the same (W = 4, 8: 6.81, 6.63 at 7, 5);
+// converting bf16, twice the conversions per byte, it wants up to two more
+// (W = 8, 16: 6.56, 6.34 at 8, 7).  An aggregate written too wants two more.
+constexpr int fused_waves(int lane_bytes, bool converts_bf16)
 {
-    return lane_bytes <= 80 ? 14 : lane_bytes <= 112 ? 12 : bf16 ? 10 : lane_bytes <= 176 ? 8 : 6;
+    const int waves = lane_bytes <= 64    ? 9
+                      : lane_bytes <= 80  ? 8
+                      : lane_bytes <= 112 ? 7
+                      : lane_bytes <= 144 ? 6
+                      : lane_bytes <= 176 ? 5
+                                          : 4;
+    return converts_bf16 ? waves + (lane_bytes <= 80 ? 0 : lane_bytes <= 144 ? 1 : 2) : waves;
 }
 
-// Resident waves per CU in fp32 mode (and for int32 contributions), by the
-// bytes of loads a lane keeps in flight: fewer bytes per wave need more
-// waves to keep enough requests in flight, more bytes fewer.  Interleaved
-// A/B of the fused call at n = 4e8 over caps of 6-16: 12 waves for lanes up
-// to 112 B (fp32 W <= 4, bf16 W <= 8, the optimizer step alone), 8 up to
-// 176 B (fp32 W = 5-8, bf16 W = 12, 16), 6 beyond (fp32 W = 12, 16).
-constexpr int fp32_mode_waves(int lane_bytes)
+// The same for the aggregation alone, and for the many-tensor kernel, whose
+// waves look their tensor up before their loads.
+constexpr int aggregate_waves(int lane_bytes, bool converts_bf16)
 {
-    return lane_bytes <= 112 ? 12 : lane_bytes <= 176 ? 8 : 6;
+    return lane_bytes <= 112 ? 12 : converts_bf16 ? 10 : lane_bytes <= 176 ? 8 : 6;
 }
 
 // The same for the run-time worker-count kernel, from the actual W: whole
@@ -646,7 +783,10 @@ int occupancy_lds_bytes(int blocks_per_cu)
             per_cu <= 0) {
             b = -1;  // unknown: launch without a cap
         } else {
-            b = (per_cu / blocks_per_cu) & ~1023;
+            // in whole LDS allocation units (1280 bytes on gfx950), so that
+            // `blocks_per_cu` blocks fit and not one fewer
+            constexpr int kLdsUnit = 1280;
+            b = per_cu / blocks_per_cu / kLdsUnit * kLdsUnit;
             if (b > per_block)
                 b = per_block;
             if (b <= 0)
@@ -759,9 +899,10 @@ hipError_t launch_vector(const LaunchArgs &a, Shape shape, hipStream_t stream)
     if (shape.shared)
         base = kConverts ? kSharedWavesConverting : kSharedWaves;
     else
-        base = W == 0      ? runtime_w_waves(a.W, GT, MODE)
-               : kConverts ? fixed_mode_waves(kLaneBytes, GT == kGradBF16)
-                           : fp32_mode_waves(kLaneBytes);
+        base = W == 0 ? runtime_w_waves(a.W, GT, MODE)
+               : ADAM ? fused_waves(kLaneBytes, kConverts && GT == kGradBF16) +
+                            (a.agg_f32 || a.agg_i32 ? 2 : 0)
+                      : aggregate_waves(kLaneBytes, kConverts && GT == kGradBF16);
     return launch_kernel(reinterpret_cast<const void *>(&vector_kernel<W, GT, MODE, ADAM>), blocks,
                          shape.lanes, a, stream,
                          occupancy_lds_bytes(blocks_per_cu_cap(base, shape.lanes, stream)));
@@ -827,9 +968,8 @@ hipError_t launch_multi_w(const MultiArgs &a, hipStream_t stream)
     constexpr int kGradBytes = GT == kGradBF16 ? 2 : 4;
     constexpr int kLaneBytes = W > 0 ? 4 * (W * kGradBytes + 12) : 1 << 30;
     constexpr bool kConverts = MODE == kAggFixed && GT != kGradI32;
-    const int base = W == 0    ? runtime_w_waves(a.W, GT, MODE)
-                     : kConverts ? fixed_mode_waves(kLaneBytes, GT == kGradBF16)
-                                 : fp32_mode_waves(kLaneBytes);
+    const int base = W == 0 ? runtime_w_waves(a.W, GT, MODE)
+                            : aggregate_waves(kLaneBytes, kConverts && GT == kGradBF16);
     const int lds = occupancy_lds_bytes(blocks_per_cu_cap(base, kWaveBlock, stream));
     const int64_t blocks = clamp_grid(a.tile_start[a.count], kWaveBlock);
     void *args[] = {const_cast<MultiArgs *>(&a)};
