@@ -63,7 +63,7 @@
  *             arrays, 8 for bf16), e.g. any sub-range of aligned arrays: the
  *             first few elements (up to 255, reaching a common 256- or
  *             64-element boundary when the arrays agree that far) are done
- *             one by one.
+ *             beside the rest.
  *             Arrays with unrelated offsets take them too when every array
  *             is aligned to its element size and the bf16 arrays can reach
  *             4-byte boundaries together: the first output is brought to a
@@ -264,8 +264,11 @@ disdp_status_t disdp_aggregate_adam_dev(const void *const *grads, int W,
 /* disdp_aggregate_adam over T tensors of one optimizer step (Section III-D,
  * step 5, applied tensor by tensor): for a shard whose tensors live in
  * separate buffers, one launch serves a batch of tensors instead of one
- * launch each (up to 48 tensors and 320 pointers per launch).  Equal, bit
- * for bit, to T disdp_aggregate_adam calls with the same hyperparameters.
+ * launch each (as many as 4 KiB of kernel arguments describe: 38 tensors
+ * with W = 8, or some 230 when they lie at one element offset in every array, as
+ * slices of flat buffers do; tensors that follow one another without a gap
+ * in every array are run as one).  Equal, bit for bit, to T
+ * disdp_aggregate_adam calls with the same hyperparameters.
  *   T               number of tensors, 0 <= T <= 65536.
  *   n               host array of T element counts (each 0 .. 2^56).
  *   grads           host array of T*W device pointers: contribution w of

@@ -560,10 +560,15 @@ disdp_status_t disdp_aggregate_adam_multi(const void *const *grads, int W,
             return DISDP_ERR_INVALID_ARG;
     }
 
-    // Batches of tensors per launch; a tensor the vector kernels cannot
-    // take goes through the single-tensor path (the element kernel).
+    // Batches of tensors; a tensor the vector kernels cannot take goes
+    // through the single-tensor path (the element kernel).  Tensors that
+    // follow one another without a gap in every array (sub-ranges of flat
+    // shard arrays) are one tensor to the kernels: an element's result does
+    // not depend on which call it is part of.
     disdp::MultiArgs ma;
-    std::memset(&ma, 0, sizeof ma);
+    ma.count = 0;
+    ma.s = disdp::StepScalars{};
+    ma.tile_start[0] = 0;
     ma.W = W;
     ma.gdtype = gdtype;
     ma.mode = mode;
@@ -583,9 +588,30 @@ disdp_status_t disdp_aggregate_adam_multi(const void *const *grads, int W,
         ma.count = 0;
         return e == hipSuccess;
     };
-    for (int j = 0; j < T; ++j) {
+    // whether tensor k starts where `len` elements from tensor j's start end
+    auto follows = [&](int j, int64_t len, int k) -> bool {
+        for (int w = 0; w < W; ++w)
+            if (static_cast<const char *>(grads[static_cast<int64_t>(j) * W + w]) + len * gb !=
+                grads[static_cast<int64_t>(k) * W + w])
+                return false;
+        if (param[j] + len != param[k] || m[j] + len != m[k] || v[j] + len != v[k])
+            return false;
+        uint16_t *cj = param_bf16_out ? param_bf16_out[j] : nullptr;
+        uint16_t *ck = param_bf16_out ? param_bf16_out[k] : nullptr;
+        return cj ? cj + len == ck : !ck;
+    };
+    for (int j = 0, next; j < T; j = next) {
+        next = j + 1;
         if (n[j] == 0)
             continue;
+        int64_t len = n[j];
+        for (; next < T; ++next) {
+            if (n[next] == 0)
+                continue;
+            if (len > kMaxN - n[next] || !follows(j, len, next))
+                break;
+            len += n[next];
+        }
         const void *const *gj = grads + static_cast<int64_t>(j) * W;
         uint16_t *p16 = param_bf16_out ? param_bf16_out[j] : nullptr;
         const void *ptrs[disdp::kMaxW + 4];
@@ -604,9 +630,9 @@ disdp_status_t disdp_aggregate_adam_multi(const void *const *grads, int W,
             ptrs[np] = p16;
             sizes[np++] = 2;
         }
-        const int head = vector_head(ptrs, sizes, np, /*ref=*/W, n[j]);
+        const int head = vector_head(ptrs, sizes, np, /*ref=*/W, len);
         if (head < 0) {
-            st = run(gj, W, gdtype, n[j], mode, frac_bits, param[j], m[j], v[j], p16, nullptr,
+            st = run(gj, W, gdtype, len, mode, frac_bits, param[j], m[j], v[j], p16, nullptr,
                      nullptr, hp, /*adam=*/true, /*agg_f32_required=*/false, stream,
                      /*scalars_in_memory=*/s_dev != nullptr, s_dev);
             if (st != DISDP_OK)
@@ -624,7 +650,7 @@ disdp_status_t disdp_aggregate_adam_multi(const void *const *grads, int W,
         slot[W + 1] = m[j] + head;
         slot[W + 2] = v[j] + head;
         slot[W + 3] = p16 ? p16 + head : nullptr;
-        ma.n[c] = n[j] - head;
+        ma.n[c] = len - head;
         ma.head[c] = head;
         const int64_t groups = ma.n[c] >> 2;
         const int64_t tiles =
