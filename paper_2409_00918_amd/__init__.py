@@ -73,6 +73,7 @@ class DisdpError(RuntimeError):
 
 
 _lib = None
+_BINDING_PATH = os.path.join(_PKG, "_binding.so")
 
 
 def hip_runtimes_mapped() -> list:
@@ -128,8 +129,37 @@ def lib() -> ctypes.CDLL:
                                                  ctypes.POINTER(AdamWHParams), vp, vp]
         L.disdp_status_string.restype = ctypes.c_char_p
         L.disdp_status_string.argtypes = [ci]
+        _bind(L, torch)
         _lib = L
     return _lib
+
+
+# Operations of the native half (see _binding's call).
+_AGGREGATE, _ADAM_STEP, _FUSED, _FUSED_DEV, _QUANTIZE = range(5)
+
+
+def _bind(L: ctypes.CDLL, torch) -> None:
+    """Gives the native half of the binding the library's functions, and makes
+    it the way calls in the ordinary form take."""
+    global _call
+    if not os.path.exists(_BINDING_PATH):
+        raise RuntimeError(f"{_BINDING_PATH} is missing: build it with "
+                           "`python -m paper_2409_00918_amd.build`")
+    from . import _binding
+    _binding.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        L.disdp_aggregate, L.disdp_adam_step, L.disdp_aggregate_adam,
+        L.disdp_aggregate_adam_dev, L.disdp_quantize)),
+        getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device,
+        getattr(torch._C, "_cuda_getCurrentRawStream", None) or _current_stream_handle)
+    _call = _binding.call
+
+
+def _call(*args) -> int:
+    """A status of the library, or -1 when the call is not in the ordinary
+    form (plain device tensors on the current GPU, builtin numbers) and is
+    left to the Python code below."""
+    lib()                       # replaces this function
+    return _call(*args)
 
 
 def status_string(status: int) -> str:
@@ -324,6 +354,11 @@ def aggregate(grads, *, mode="fp32", frac_bits: int = 0, agg_out_f32=None,
               agg_out_i32=None, stream=None) -> None:
     """W-way reduction of `grads` (float32 or bf16 device tensors of one
     length) into `agg_out_f32` and/or `agg_out_i32` (int32, fixed mode)."""
+    if stream is None:
+        st = _call(_AGGREGATE, grads, None, None, None, None, agg_out_f32, agg_out_i32, None,
+                   mode, frac_bits, None, None, None, None, None, None, None)
+        if st >= 0:
+            return _check(st, "disdp_aggregate")
     torch = _torch()
     grads, ptrs, gdt, n = _grads(grads)
     st = _launch(raw_aggregate, grads + [agg_out_f32, agg_out_i32], stream,
@@ -336,6 +371,11 @@ def aggregate(grads, *, mode="fp32", frac_bits: int = 0, agg_out_f32=None,
 def adam_step(grad, param, m, v, param_bf16_out=None, *, lr, beta1, beta2,
               eps, weight_decay, step, grad_scale=1.0, stream=None) -> None:
     """One AdamW step on (param, m, v) in place from the fp32 aggregate."""
+    if stream is None:
+        st = _call(_ADAM_STEP, grad, param, m, v, param_bf16_out, None, None, None, None, None,
+                   lr, beta1, beta2, eps, weight_decay, step, grad_scale)
+        if st >= 0:
+            return _check(st, "disdp_adam_step")
     torch = _torch()
     n = param.numel()
     f32 = (torch.float32,)
@@ -354,6 +394,11 @@ def aggregate_adam(grads, param, m, v, param_bf16_out=None, *, lr, beta1,
                    mode="fp32", frac_bits: int = 0, agg_out_f32=None,
                    agg_out_i32=None, stream=None) -> None:
     """Aggregate `grads` and take one AdamW step, in one pass."""
+    if stream is None:
+        st = _call(_FUSED, grads, param, m, v, param_bf16_out, agg_out_f32, agg_out_i32, None,
+                   mode, frac_bits, lr, beta1, beta2, eps, weight_decay, step, grad_scale)
+        if st >= 0:
+            return _check(st, "disdp_aggregate_adam")
     torch = _torch()
     grads, ptrs, gdt, n = _grads(grads)
     f32 = (torch.float32,)
@@ -388,6 +433,11 @@ def aggregate_adam_dev(grads, param, m, v, param_bf16_out=None, *, scalars,
     `scalars`: a float32 tensor of 10 elements (a StepScalars image, e.g.
     filled by copying step_scalars(...)), on the device or pinned host
     memory.  Lets one captured HIP graph serve every step."""
+    if stream is None:
+        st = _call(_FUSED_DEV, grads, param, m, v, param_bf16_out, agg_out_f32, agg_out_i32,
+                   scalars, mode, frac_bits, None, None, None, None, None, None, None)
+        if st >= 0:
+            return _check(st, "disdp_aggregate_adam_dev")
     torch = _torch()
     grads, ptrs, gdt, n = _grads(grads)
     f32 = (torch.float32,)
@@ -483,6 +533,11 @@ def aggregate_adam_multi(tensors, *, lr=None, beta1=None, beta2=None, eps=None,
 def quantize(grad, out, *, frac_bits: int, stream=None) -> None:
     """out (int32) = the switch's integer format of `grad` (float32 or bf16)
     at scale 2^frac_bits, saturating."""
+    if stream is None:
+        st = _call(_QUANTIZE, grad, None, None, None, None, None, out, None, None, frac_bits,
+                   None, None, None, None, None, None, None)
+        if st >= 0:
+            return _check(st, "disdp_quantize")
     torch = _torch()
     n = grad.numel()
     gdt = _grad_dtype(grad)

@@ -128,6 +128,27 @@ bool gpu_addressable(const void *p, bool *device_memory = nullptr)
     }
 }
 
+// The allocation that device memory `p` lies in: [lo, lo + size), or size 0
+// when the runtime does not say.
+struct Allocation {
+    uintptr_t lo;
+    size_t size;
+};
+
+Allocation allocation_of(const void *p)
+{
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    const hipError_t pending = hipPeekAtLastError();
+    if (hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
+        if (pending == hipSuccess)
+            (void)hipGetLastError();  // as in gpu_addressable
+        return Allocation{0, 0};
+    }
+    const uintptr_t lo = reinterpret_cast<uintptr_t>(base);
+    return Allocation{lo, reinterpret_cast<uintptr_t>(p) - lo < size ? size : 0};
+}
+
 // gpu_addressable over the many pointers of one call: the device (or
 // managed) allocations already confirmed in this call are remembered, and a
 // pointer inside one of them needs no further query of the runtime.  Arrays
@@ -137,28 +158,21 @@ class AddressableSet {
     bool check(const void *p)
     {
         const uintptr_t a = reinterpret_cast<uintptr_t>(p);
-        if (a - last_lo_ < last_size_)
+        if (a - last_.lo < last_.size)
             return true;
         auto it = known_.upper_bound(a);  // first allocation starting above a
         if (it != known_.begin() && a - std::prev(it)->first < std::prev(it)->second) {
-            last_lo_ = std::prev(it)->first;
-            last_size_ = std::prev(it)->second;
+            last_ = Allocation{std::prev(it)->first, std::prev(it)->second};
             return true;
         }
         bool device_memory = false;
         if (!gpu_addressable(p, &device_memory))
             return false;
         if (device_memory) {
-            hipDeviceptr_t base = nullptr;
-            size_t size = 0;
-            const hipError_t pending = hipPeekAtLastError();
-            if (hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) == hipSuccess &&
-                a - reinterpret_cast<uintptr_t>(base) < size) {
-                last_lo_ = reinterpret_cast<uintptr_t>(base);
-                last_size_ = size;
-                known_[last_lo_] = size;
-            } else if (pending == hipSuccess) {
-                (void)hipGetLastError();  // as in gpu_addressable
+            const Allocation at = allocation_of(p);
+            if (at.size) {
+                last_ = at;
+                known_[at.lo] = at.size;
             }
         }
         return true;
@@ -166,8 +180,39 @@ class AddressableSet {
 
   private:
     std::map<uintptr_t, size_t> known_;  // allocation start -> size
-    uintptr_t last_lo_ = 0;
-    size_t last_size_ = 0;
+    Allocation last_{0, 0};
+};
+
+// The same for the dozen pointers of a single call: a short list, and no
+// further questions about allocations once three pointers in a row lay
+// outside those before (large arrays have allocations of their own, and
+// asking for each costs as much again as the query it saves).
+class FewAddressable {
+  public:
+    bool check(const void *p)
+    {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+        for (int i = 0; i < count_; ++i)
+            if (a - known_[i].lo < known_[i].size) {
+                misses_ = 0;
+                return true;
+            }
+        bool device_memory = false;
+        if (!gpu_addressable(p, &device_memory))
+            return false;
+        if (device_memory && count_ < kMost && misses_ < 3) {
+            ++misses_;
+            const Allocation at = allocation_of(p);
+            if (at.size)
+                known_[count_++] = at;
+        }
+        return true;
+    }
+
+  private:
+    static constexpr int kMost = 8;
+    Allocation known_[kMost];
+    int count_ = 0, misses_ = 0;
 };
 
 // A vector kernel's tile is 256 elements (a one-wave block of 64 lanes x 4
@@ -307,14 +352,15 @@ disdp_status_t run(const void *const *grads, int W, int gdtype, int64_t n,
     }
 
     // Every array must be addressable by the GPU as given (first HIP call).
+    FewAddressable addressable;
     for (int w = 0; w < W; ++w)
-        if (!gpu_addressable(grads[w]))
+        if (!addressable.check(grads[w]))
             return DISDP_ERR_INVALID_ARG;
     for (const void *p : {static_cast<const void *>(param), static_cast<const void *>(m),
                           static_cast<const void *>(v), static_cast<const void *>(p16),
                           static_cast<const void *>(agg_f32), static_cast<const void *>(agg_i32),
                           static_cast<const void *>(s_dev)})
-        if (p && !gpu_addressable(p))
+        if (p && !addressable.check(p))
             return DISDP_ERR_INVALID_ARG;
 
     LaunchArgs a;

@@ -1,0 +1,119 @@
+"""The native half of the binding: it takes calls in the ordinary form and
+leaves every other to the Python code, without having done anything.  On the
+GPU, both ways must give the same bits and the same errors."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2409_00918_amd as dd
+
+KW = dict(lr=1e-4, beta1=0.9, beta2=0.95, eps=1e-8, weight_decay=0.1, step=3)
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+def _native(op, grads, p=None, m=None, v=None, c=None, af=None, ai=None, sc=None, mode="fp32",
+            frac=0, step=1):
+    dd.lib()
+    return dd._call(op, grads, p, m, v, c, af, ai, sc, mode, frac, 1e-4, 0.9, 0.95, 1e-8, 0.1,
+                    step, 1.0)
+
+
+@pytest.mark.parametrize("grads", [
+    lambda: [torch.zeros(8)] * 2,                                   # host tensors
+    lambda: (torch.zeros(8) for _ in range(2)),                     # an iterator (not consumed)
+    lambda: [], lambda: None, lambda: [1, 2], lambda: [torch.zeros(8)] * 65,
+    lambda: [torch.zeros(8).as_subclass(Sub)], lambda: [torch.zeros(8, dtype=torch.float64)]])
+def test_other_forms_are_left_to_python(grads):
+    out = torch.zeros(8)
+    g = grads()
+    assert _native(dd._AGGREGATE, g, af=out) == -1
+    if hasattr(g, "__next__"):
+        assert len(list(g)) == 2
+    assert _native(dd._FUSED, g, p=out, m=out, v=out) == -1
+
+
+def test_odd_arguments_are_left_to_python():
+    g = [torch.zeros(8)]
+    assert _native(dd._AGGREGATE, g, mode="float") == -1
+    assert _native(dd._AGGREGATE, g, frac=2.0) == -1
+    assert _native(dd._AGGREGATE, g, frac=1 << 40) == -1
+    assert _native(dd._FUSED, g, step=1 << 70) == -1
+    assert _native(dd._FUSED, g, step="x") == -1
+    assert _native(9, g) == -1
+    with pytest.raises(TypeError):
+        dd._call(0)
+    with pytest.raises(ValueError):
+        dd.aggregate([torch.zeros(8)], mode="float", agg_out_f32=torch.zeros(8))
+
+
+def _tensors(n, W, gdtype):
+    gen = torch.Generator(device="cuda").manual_seed(n + W)
+    def r(scale):
+        return torch.randn(n, generator=gen, device="cuda") * scale
+    g = [r(1e-4) for _ in range(W)]
+    if gdtype == "bf16":
+        g = [x.bfloat16() for x in g]
+    elif gdtype == "i32":
+        g = [(x * 2.0**24).round().int() for x in g]
+    return g, r(0.02), r(1e-4), r(1e-4) ** 2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 4099])
+@pytest.mark.parametrize("gdtype,mode", [("f32", "fp32"), ("bf16", "fp32"), ("f32", "fixed"),
+                                         ("i32", "fixed")])
+def test_both_ways_give_the_same_bits(n, gdtype, mode):
+    g, p, m, v = _tensors(n, 3, gdtype)
+    sc = torch.frombuffer(bytearray(dd.step_scalars(**KW)), dtype=torch.float32).cuda()
+    here = torch.cuda.current_stream()               # an explicit stream: the Python way
+    got = []
+    for stream in (None, here):
+        out = []
+        for op in ("fused", "dev", "adam", "aggregate", "quantize"):
+            P, M, V = torch.nn.Parameter(p.clone()), m.clone(), v.clone()
+            c = torch.zeros(n, dtype=torch.int16, device="cuda")
+            af = torch.zeros(n, device="cuda")
+            ai = torch.zeros(n, dtype=torch.int32, device="cuda") if mode == "fixed" else None
+            agg = dict(mode=mode, frac_bits=24, agg_out_f32=af, agg_out_i32=ai, stream=stream)
+            if op == "fused":
+                dd.aggregate_adam(tuple(g), P, M, V, c, **KW, **agg)
+            elif op == "dev":
+                dd.aggregate_adam_dev(g, P, M, V, c, scalars=sc, **agg)
+            elif op == "adam":
+                dd.adam_step(m, P, M.add_(1e-6), V, None, **KW, stream=stream)
+            elif op == "aggregate":
+                dd.aggregate(g, **agg)
+            elif gdtype != "i32":
+                ai = torch.zeros(n, dtype=torch.int32, device="cuda")
+                dd.quantize(g[0], ai, frac_bits=20, stream=stream)
+            torch.cuda.synchronize()
+            out += [x.detach().cpu().numpy().tobytes() for x in (P, M, V, c, af, ai)
+                    if x is not None]
+        got.append(out)
+    assert got[0] == got[1]
+
+
+@pytest.mark.gpu
+def test_both_ways_raise_the_same_errors():
+    g, p, m, v = _tensors(64, 2, "f32")
+    here = torch.cuda.current_stream()
+    wide = torch.zeros(128, device="cuda")
+    def fused(stream, grads=g, P=p, M=m, V=v, c=None, **kw):
+        dd.aggregate_adam(grads, P, M, V, c, stream=stream, **{**KW, **kw})
+    bad = [dict(P=m), dict(step=0), dict(grads=[]), dict(grads=[g[0], wide]), dict(P=wide[::2]),
+           dict(M=m.double()), dict(c=torch.zeros(64, device="cuda")), dict(V=v.cpu()),
+           dict(mode="mean"), dict(lr="x"), dict(beta1=1.0), dict(grads=[g[0], g[1].bfloat16()]),
+           dict(grads=[x.int() for x in g]), dict(P=None)]
+    for kw in bad:
+        seen = []
+        for stream in (None, here):
+            with pytest.raises(Exception) as e:
+                fused(stream, **kw)
+            seen.append((type(e.value), str(e.value)))
+        assert seen[0] == seen[1], kw
+    with pytest.raises(Exception):
+        torch.func.vmap(lambda x: fused(None, P=x))(torch.stack([p, p]))
+    assert np.isfinite(p.cpu().numpy()).all()
