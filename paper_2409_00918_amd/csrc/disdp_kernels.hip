@@ -606,12 +606,13 @@ struct Split {
     int lead;        // blocks in front of the tile of group 0
     int singles;     // whether the first of them is the block of single elements
     int head, tail;
+    int together;    // log2 of how many tiles in a row fall to one XCD
 };
 
-__host__ __device__ constexpr Split make_split(int64_t n_groups, int head, int tail)
+__host__ __device__ constexpr Split make_split(int64_t n_groups, int head, int tail, int together)
 {
     const int singles = (head & 3) || tail ? 1 : 0;
-    return Split{n_groups, singles + (head >= 4 ? 1 : 0), singles, head, tail};
+    return Split{n_groups, singles + (head >= 4 ? 1 : 0), singles, head, tail, together};
 }
 
 // The kernel arguments: what a wave needs before its loads first, the
@@ -661,7 +662,14 @@ __device__ __forceinline__ void deal(const Split &sp, int block, int lanes_log2,
             f(Single{in_head ? int64_t(lane) - sp.head : 4 * sp.n_groups + lane - 4});
         return;
     }
-    const int64_t grp0 = int64_t(block - sp.lead) << lanes_log2;
+    // Blocks go to the 8 XCDs in turn: 2^together tiles in a row are every
+    // eighth of 8 << together blocks (where those are whole).
+    int tile = block - sp.lead;
+    const int last = tile | ((8 << sp.together) - 1);
+    if (sp.together && tile >= 0 && (int64_t(last) + 1) << lanes_log2 <= sp.n_groups)
+        tile = last - (8 << sp.together) + 1 + ((tile & 7) << sp.together) +
+               ((tile >> 3) & ((1 << sp.together) - 1));
+    const int64_t grp0 = int64_t(tile) << lanes_log2;
     // lanes [from, to) have a group: every lane but in the last tile and the
     // head's (the one with grp0 < 0)
     const int64_t left = sp.n_groups - grp0;
@@ -685,9 +693,10 @@ __global__ DISDP_LAUNCH_BOUNDS void vector_kernel(VectorArgs<W> k)
     if constexpr (W > 0) {
 #define G(i) "s"(a.g[i < W ? i : W - 1])
         asm volatile("" ::"s"(k.split.n_groups), "s"(k.split.lead), "s"(k.split.singles),
-                     "s"(k.split.head), "s"(k.split.tail), "s"(k.lanes_log2), "s"(a.p), "s"(a.m),
-                     "s"(a.v), G(0), G(1), G(2), G(3), G(4), G(5), G(6), G(7), G(8), G(9), G(10),
-                     G(11), G(12), G(13), G(14), G(15));
+                     "s"(k.split.head), "s"(k.split.tail), "s"(k.split.together),
+                     "s"(k.lanes_log2), "s"(a.p), "s"(a.m),
+                     "s"(a.v), G(0), G(1), G(2), G(3), G(4), G(5), G(6), G(7), G(8), G(9),
+                     G(10), G(11), G(12), G(13), G(14), G(15));
 #undef G
     }
     deal(k.split, blockIdx.x, k.lanes_log2, [&](auto at) {
@@ -785,7 +794,7 @@ __global__ DISDP_WAVE_LAUNCH_BOUNDS void multi_kernel(MultiLaunch k)
 #undef G
     }
     const int last = shape >> 10;
-    Split sp = make_split(0, shape & 255, (shape >> 8) & 3);
+    Split sp = make_split(0, shape & 255, (shape >> 8) & 3, 0);
     if (last)
         sp.n_groups = (int64_t(end - here) - sp.lead - 1) * kWave + last;
     constexpr int kGradBytes = GT == kGradBF16 ? 2 : 4;
@@ -905,10 +914,10 @@ constexpr int aggregate_waves(int lane_bytes, bool converts_bf16)
 // 6.35, 6.09, 6.08 (5: 6.20, 6.34, 6.02, 6.02; 3: 5.6-5.9); bf16 W = 9, 13 10:
 // 6.45, 6.38; W = 20 7: 6.36; W = 24, 32, 64 6: 6.21, 6.04, 5.78 (5: 6.14,
 // 6.12, 5.82).  Fixed point converting fp32 the same but 5 from W = 16 on (W =
-// 24, 64: 6.25, 6.02; 4: 5.92, 5.84), converting bf16 two more (W = 24, 64:
-// 6.22, 5.97).  The aggregation alone: fp32 W = 9 9: 6.48; W = 24, 32, 64 6:
-// 6.15, 6.13, 6.14-6.39; bf16 W = 10 14: 6.19; W = 24 9: 6.11; W = 32, 64 8:
-// 6.04, 6.03.
+// 24, 64: 6.25, 6.02; 4: 5.92, 5.84), converting bf16 two or three more (W =
+// 24, 32, 64 at 8, 9, 9: 6.22, 6.07, 6.03).  The aggregation alone: fp32 W = 9
+// 9: 6.48; W = 24, 32, 64 6: 6.15, 6.13, 6.14-6.39; bf16 W = 10 14: 6.19; W = 24
+// 9: 6.11; W = 32, 64 8: 6.04, 6.03.
 int runtime_w_waves(int W, int gt, int mode, bool adam)
 {
     const bool bf16 = gt == kGradBF16;
@@ -916,7 +925,7 @@ int runtime_w_waves(int W, int gt, int mode, bool adam)
     if (!adam)
         return bf16 ? (W < 16 ? 14 : W < 32 ? 9 : 8) : W < 16 ? 9 : 6;
     if (bf16)
-        return (W < 16 ? 10 : W < 24 ? 7 : 6) + (converts ? 2 : 0);
+        return (W < 16 ? 10 : W < 24 ? 7 : 6) + (converts ? (W < 32 ? 2 : 3) : 0);
     return W < 16 ? 7 : W < 24 || converts ? 5 : 4;
 }
 
@@ -1106,6 +1115,47 @@ void advance(VectorArgs<W> &k, int64_t elems, int grad_bytes)
         k.g[w] += elems * grad_bytes;
 }
 
+// Tiles in a row that one XCD takes, as a log2: 1 for large launches over many
+// bf16 contributions.  A bf16 tile is 512 bytes of each; two neighbours on one
+// XCD make a 1 KiB read of it, as one fp32 tile is (together / one by one, each
+// at its own best cap, TB/s, on two or more layouts each): fused W = 16
+// 6.74 / 6.51 (n = 2.5e7), 6.60 / 6.43 (2e8), 6.51 / 6.49 (5e8); W = 12
+// 6.55 / 6.49; W = 20, 32, 64 6.53 / 6.34, 6.32 / 6.13, 6.11 / 5.99; the
+// aggregation alone W = 16, 24, 32, 64 6.39 / 6.32, 6.27 / 6.10, 6.29 / 6.05,
+// 6.06 / 5.88; fixed point, fused W = 16 6.51 / 6.35.  Fewer contributions
+// gain under 1% or lose (W = 4, 8; the aggregation of 4 and 8: -2%), a launch
+// of a few rounds loses (fused W = 16, n = 4e6 -1.5%, 1e6 -5%), fp32 too (W =
+// 1, 4, 8: -1%, -1%, -2%).  It also loses when the arrays lie a multiple of 64
+// MiB apart, where the same tile of every array falls to the same channels:
+// fused W = 16, arrays 128 and 256 pages of 2 MiB apart 5.2 / 6.2 and 5.1 /
+// 6.3, 127 and 129 pages 5.4 / 6.2 and 4.9 / 6.2, 32 pages 6.2 / 6.3 (4 and
+// 8 tiles together did not do better over the layouts).
+int tiles_together(const LaunchArgs &a, bool adam, int base_waves)
+{
+    constexpr int kRounds = 16;
+    constexpr uintptr_t kRepeat = uintptr_t(64) << 20, kNear = uintptr_t(4) << 20;
+    if (a.gdtype != kGradBF16 || a.W < (adam ? 12 : 16) ||
+        ceil_div(a.n >> 2, kWave) <= int64_t(kRounds) * base_waves * cu_count())
+        return 0;
+    for (int w = 1; w < a.W; ++w) {
+        const uintptr_t apart = reinterpret_cast<uintptr_t>(a.g[w]) -
+                                reinterpret_cast<uintptr_t>(a.g[w - 1]);
+        if ((apart + kNear) % kRepeat <= 2 * kNear)
+            return 0;
+    }
+    return 1;
+}
+
+// The caps of such launches, which are flatter: fused W = 16 at 6, 7, 8, 10:
+// 6.60, 6.57, 6.52, 6.48 (fixed point at 7, 8, 10: 6.50, 6.51, 6.45; W = 64 at
+// 6, 9, 11: 5.37, 5.99, 6.01); the aggregation of 64 in fixed point at 7, 9, 11:
+// 5.94, 6.17, 6.10.
+constexpr int together_waves(int W, bool adam, bool converts)
+{
+    return adam ? (W <= 16 ? 7 : W < 32 ? 8 : W < 48 ? 7 : 6) + (!converts ? 0 : W <= 16 ? 1 : 3)
+                : (W < 32 ? 9 : 7) + 2 * converts;
+}
+
 template <int W, int GT, int MODE, bool ADAM>
 hipError_t launch_vector(const LaunchArgs &a, Shape shape, hipStream_t stream)
 {
@@ -1114,13 +1164,16 @@ hipError_t launch_vector(const LaunchArgs &a, Shape shape, hipStream_t stream)
     constexpr int kGradBytes = GT == kGradBF16 ? 2 : 4;
     constexpr int kLaneBytes = W > 0 ? 4 * (W * kGradBytes + (ADAM ? 12 : 0)) : 1 << 30;
     constexpr bool kConverts = MODE == kAggFixed && GT != kGradI32;
-    int base;
+    int base, together = 0;
     if (shape.shared) {
         base = kConverts ? kSharedWavesConverting : kSharedWaves;
     } else {
         base = W == 0 ? runtime_w_waves(a.W, GT, MODE, ADAM)
                : ADAM ? fused_waves(kLaneBytes, kConverts && GT == kGradBF16)
                       : aggregate_waves(kLaneBytes, kConverts && GT == kGradBF16);
+        together = tiles_together(a, ADAM, base);
+        if (together)
+            base = together_waves(a.W, ADAM, kConverts);
         if (ADAM && (a.agg_f32 || a.agg_i32))
             base += 2;
         if (ceil_div(a.n >> 2, kWave) <= int64_t(kUncappedRounds) * base * cu_count())
@@ -1134,7 +1187,7 @@ hipError_t launch_vector(const LaunchArgs &a, Shape shape, hipStream_t stream)
         const int64_t most = (max_blocks(shape.lanes) - 2) * shape.lanes;
         const int64_t now = left < most ? left : most;
         left -= now;
-        k.split = make_split(now, head, left ? 0 : static_cast<int>(a.n & 3));
+        k.split = make_split(now, head, left ? 0 : static_cast<int>(a.n & 3), together);
         const int64_t blocks = k.split.lead + ceil_div(now, shape.lanes);
         void *args[] = {&k};
         const hipError_t e = hipLaunchKernel(
@@ -1296,7 +1349,7 @@ hipError_t launch_multi_w(const MultiArgs &a, hipStream_t stream)
         Split sp[kMultiMost];
         for (; take < most; ++take) {
             const int64_t n = a.n[i + take];
-            sp[take] = make_split(n >> 2, a.head[i + take], static_cast<int>(n & 3));
+            sp[take] = make_split(n >> 2, a.head[i + take], static_cast<int>(n & 3), 0);
             const int64_t add = sp[take].lead + ceil_div(sp[take].n_groups, kWave);
             if (blocks + add > max_blocks(kWave))
                 break;
@@ -1399,7 +1452,7 @@ hipError_t launch_quantize(const QuantizeArgs &q, bool vector_path, hipStream_t 
         const int64_t most = (max_blocks(kWave) - 2) * kWave;
         const int64_t now = left < most ? left : most;
         left -= now;
-        k.split = make_split(now, head, left ? 0 : static_cast<int>(q.n & 3));
+        k.split = make_split(now, head, left ? 0 : static_cast<int>(q.n & 3), 0);
         const int64_t blocks = k.split.lead + ceil_div(now, kWave);
         void *args[] = {&k};
         const hipError_t e = hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)), dim3(kWave),
