@@ -246,8 +246,9 @@ __device__ __forceinline__ float div_mid(float n, float d)
     return __builtin_fmaf(__builtin_fmaf(-d, q, n), y, q);
 }
 
-// adamw on the four elements of a lane, the same bits in about half the
-// instructions (372 -> 226 vector instructions for the W = 8 fp32 group).
+// adamw on the four elements of a lane, the same bits in fewer instructions
+// (a W = 8 fp32 group 316 -> 215 vector instructions, 30 of them while its
+// loads are in flight).
 // The kernel is bound by memory at shard sizes, but a launch of a few
 // megabytes runs its waves in step -- all load, all compute, all store -- and
 // the arithmetic adds to its time.  The short divisions and square root need
@@ -939,16 +940,17 @@ constexpr int kUncappedRounds = 5;
 // The launch shape of the vector kernels for one call.
 //   solo   (default): one-wave blocks, occupancy caps from the tables above
 //          -- the fastest shape when the kernel has the GPU to itself.
-//   shared (DISDP_LAUNCH_SHAPE=shared in the environment): four-wave blocks
-//          capped at 12 waves per CU, 20 for fixed-point kernels that
-//          convert float contributions.  Next to a bf16 GEMM loop on
-//          another stream of the same (unmasked) GPU, the solo shape's
-//          stream of one-wave blocks refills every slot a retiring block
-//          frees and the GEMM slows about 10x while the fused call slows
-//          1.1x; a retiring four-wave block leaves a hole of four wave slots
-//          that a GEMM workgroup can take, and the two slow each other about
-//          evenly (measured 1.7x and 2.0x), at 3-5% below the solo shape's
-//          rate when alone.
+//   shared (DISDP_LAUNCH_SHAPE=shared in the environment): four-wave blocks,
+//          two of them per CU (three or four for fixed-point kernels that
+//          convert float contributions).  Next to a bf16 GEMM loop on another
+//          stream of the same (unmasked) GPU, the solo shape's stream of
+//          one-wave blocks refills every slot a retiring block frees and the
+//          GEMM slows about 10x while the fused call slows 1.1x; a retiring
+//          four-wave block leaves four wave slots and half the LDS, which a
+//          GEMM workgroup can take, and the two slow each other about evenly
+//          (measured 1.7x and 2.0x; with three blocks the hole is too small
+//          and the GEMM slows 10x again), at 3-5% below the solo shape's rate
+//          when alone (W = 8 fp32, n = 2e8, 2 blocks 6.50 TB/s, 3 6.32).
 // The variable is read on every call, so a process can switch between
 // calls; any other value means solo.
 struct Shape {
@@ -966,8 +968,10 @@ Shape launch_shape()
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-constexpr int kSharedWaves = 12;
-constexpr int kSharedWavesConverting = 20;
+constexpr int shared_waves(bool adam, bool converts)
+{
+    return !converts ? 8 : adam ? 12 : 16;
+}
 
 // Dynamic LDS bytes a vector-kernel block reserves so that at most
 // `blocks_per_cu` blocks fit on a CU (0 = no cap), cached per device.
@@ -1166,7 +1170,7 @@ hipError_t launch_vector(const LaunchArgs &a, Shape shape, hipStream_t stream)
     constexpr bool kConverts = MODE == kAggFixed && GT != kGradI32;
     int base, together = 0;
     if (shape.shared) {
-        base = kConverts ? kSharedWavesConverting : kSharedWaves;
+        base = shared_waves(ADAM, kConverts);
     } else {
         base = W == 0 ? runtime_w_waves(a.W, GT, MODE, ADAM)
                : ADAM ? fused_waves(kLaneBytes, kConverts && GT == kGradBF16)
