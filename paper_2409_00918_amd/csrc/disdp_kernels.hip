@@ -823,28 +823,49 @@ __global__ DISDP_WAVE_LAUNCH_BOUNDS void multi_kernel(MultiLaunch k)
 
 // ---- the format conversion as a producer ------------------------------------
 
-// out = quantize(g), dealt out as in vector_kernel over one-wave blocks.
+// out = quantize(g), a tile to a one-wave block; the head's groups and the
+// single elements are dealt out by the blocks in front, as in vector_kernel.  A
+// lane has one load only, so the time between a wave's start and that load
+// counts: with the general deal() for every tile the 13B/16 contribution took
+// 743 us, this way 728 (two or four tiles a wave: 775, 793).
 struct QuantizeVectorArgs {
-    Split split;
     Base g, out;
+    int64_t n_groups;
+    int lead;          // blocks in front of the tiles
     float qscale;
+    Split edges;       // of no tiles: the head and the single elements
 };
+
+template <int GT, class At>
+__device__ __forceinline__ void quantize_at(const QuantizeVectorArgs &k, At at)
+{
+    constexpr int N = At::kN;
+    float x[N];
+    int32_t y[N];
+    load_grad<GT>(k.g, at, x);
+#pragma unroll
+    for (int e = 0; e < N; ++e)
+        y[e] = quantize(x[e], k.qscale);
+    store_i32(k.out, at, y);
+}
 
 template <int GT>
 __global__ DISDP_WAVE_LAUNCH_BOUNDS void quantize_vector_kernel(QuantizeVectorArgs k)
 {
-    asm volatile("" ::"s"(k.split.n_groups), "s"(k.split.lead), "s"(k.split.singles),
-                 "s"(k.split.head), "s"(k.split.tail), "s"(k.g), "s"(k.out), "s"(k.qscale));
-    deal(k.split, blockIdx.x, 6, [&](auto at) {
-        constexpr int N = decltype(at)::kN;
-        float x[N];
-        int32_t y[N];
-        load_grad<GT>(k.g, at, x);
-#pragma unroll
-        for (int e = 0; e < N; ++e)
-            y[e] = quantize(x[e], k.qscale);
-        store_i32(k.out, at, y);
-    });
+    const int block = static_cast<int>(blockIdx.x) - k.lead;
+    if (block >= 0) {
+        const Tile at{int64_t(block) * kWave, threadIdx.x};
+        if (at.grp0 + at.lane < k.n_groups)
+            quantize_at<GT>(k, at);
+    } else {
+        deal(k.edges, static_cast<int>(blockIdx.x), 6, [&](auto at) {
+            constexpr bool kTile = decltype(at)::kN == 4;
+            if constexpr (kTile)
+                quantize_at<GT>(k, at);
+            else
+                quantize_at<GT>(k, Single{at.i < 0 ? at.i : at.i + 4 * k.n_groups});
+        });
+    }
 }
 
 template <int GT>
@@ -1449,15 +1470,17 @@ hipError_t launch_quantize(const QuantizeArgs &q, bool vector_path, hipStream_t 
     }
     const void *fn = bf16 ? reinterpret_cast<const void *>(&quantize_vector_kernel<kGradBF16>)
                           : reinterpret_cast<const void *>(&quantize_vector_kernel<kGradF32>);
-    QuantizeVectorArgs k{{}, base_of(q.g), base_of(q.out), q.qscale};
+    QuantizeVectorArgs k{base_of(q.g), base_of(q.out), 0, 0, q.qscale, {}};
     int64_t left = q.n >> 2;  // as in launch_vector
     int head = q.head;
     do {
         const int64_t most = (max_blocks(kWave) - 2) * kWave;
         const int64_t now = left < most ? left : most;
         left -= now;
-        k.split = make_split(now, head, left ? 0 : static_cast<int>(q.n & 3), 0);
-        const int64_t blocks = k.split.lead + ceil_div(now, kWave);
+        k.n_groups = now;
+        k.edges = make_split(0, head, left ? 0 : static_cast<int>(q.n & 3), 0);
+        k.lead = k.edges.lead;
+        const int64_t blocks = k.lead + ceil_div(now, kWave);
         void *args[] = {&k};
         const hipError_t e = hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)), dim3(kWave),
                                              args, 0, stream);
