@@ -122,7 +122,8 @@ bool asked(PyObject *fn, PyObject *arg, unsigned long long &x)
 
 // call(op, grads, param, m, v, param_bf16, agg_f32, agg_i32, scalars, mode,
 // frac_bits, lr, beta1, beta2, eps, weight_decay, step, grad_scale) ->
-// status, or -1.  Arguments an operation does not take are None.
+// status, or -1.  Arguments an operation does not take are None; a None where
+// the operation takes one is the caller's, and left to the Python code.
 enum { A_OP, A_GRADS, A_P, A_M, A_V, A_P16, A_AGG_F32, A_AGG_I32, A_SCALARS, A_MODE, A_FRAC,
        A_LR, A_BETA1, A_BETA2, A_EPS, A_WD, A_STEP, A_GRAD_SCALE, A_COUNT };
 
@@ -134,7 +135,8 @@ int ordinary_call(PyObject *const *a)
         return -1;
     constexpr int64_t kIntMin = std::numeric_limits<int>::min();
     constexpr int64_t kIntMax = std::numeric_limits<int>::max();
-    if (a[A_MODE] != Py_None) {
+    const bool sums = op == kOpAggregate || op == kOpFused || op == kOpFusedDev;
+    if (sums) {
         if (PyUnicode_CheckExact(a[A_MODE])) {
             if (PyUnicode_CompareWithASCIIString(a[A_MODE], "fp32") == 0)
                 mode = DISDP_AGG_FP32;
@@ -146,7 +148,7 @@ int ordinary_call(PyObject *const *a)
             return -1;
         }
     }
-    if (a[A_FRAC] != Py_None && !integer(a[A_FRAC], kIntMin, kIntMax, frac))
+    if ((sums || op == kOpQuantize) && !integer(a[A_FRAC], kIntMin, kIntMax, frac))
         return -1;
     const bool adam = op == kOpAdamStep || op == kOpFused || op == kOpFusedDev;
     disdp_adamw_hparams_t hp{};
@@ -167,7 +169,7 @@ int ordinary_call(PyObject *const *a)
     PyObject *const *items = &a[A_GRADS];
     Py_ssize_t W = 1;
     Held held;   // a list may change while the library runs without the lock
-    if (op == kOpAggregate || op == kOpFused || op == kOpFusedDev) {
+    if (sums) {
         if (PyList_CheckExact(a[A_GRADS]))
             held.ref = PyList_AsTuple(a[A_GRADS]);
         else if (PyTuple_CheckExact(a[A_GRADS]))

@@ -114,6 +114,26 @@ def test_both_ways_raise_the_same_errors():
                 fused(stream, **kw)
             seen.append((type(e.value), str(e.value)))
         assert seen[0] == seen[1], kw
+    ai = torch.zeros(64, dtype=torch.int32, device="cuda")
+    sc = torch.zeros(10, device="cuda")
+    # a caller's None is not "an argument this operation does not take"
+    nones = [lambda s: fused(s, mode=None), lambda s: fused(s, mode="fixed", frac_bits=None),
+             lambda s: dd.aggregate(g, mode=None, agg_out_f32=wide[:64], stream=s),
+             lambda s: dd.aggregate(g, frac_bits=None, agg_out_f32=wide[:64], stream=s),
+             lambda s: dd.aggregate_adam_dev(g, p, m, v, scalars=sc, mode=None, stream=s),
+             lambda s: dd.aggregate_adam_dev(g, p, m, v, scalars=sc, frac_bits=None, stream=s),
+             lambda s: dd.aggregate_adam_dev(g, p, m, v, scalars=None, stream=s),
+             lambda s: dd.quantize(g[0], ai, frac_bits=None, stream=s),
+             lambda s: dd.quantize(g[0], None, frac_bits=20, stream=s),
+             lambda s: fused(s, lr=None), lambda s: fused(s, step=None)]
+    for k, call in enumerate(nones):
+        seen = []
+        for stream in (None, here):
+            with pytest.raises(Exception) as e:
+                call(stream)
+            seen.append((type(e.value), str(e.value)))
+        assert seen[0] == seen[1], k
+    assert not wide.any() and not ai.any()
     with pytest.raises(Exception):
         torch.func.vmap(lambda x: fused(None, P=x))(torch.stack([p, p]))
     assert np.isfinite(p.cpu().numpy()).all()
