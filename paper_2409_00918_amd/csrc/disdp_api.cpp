@@ -222,11 +222,14 @@ class FewAddressable {
 // 256 or 512), so the head reaches a 256-element boundary when it can.
 constexpr int kTileElems = 256;
 
-// Elements to do one by one before the vector kernels can take arrays
+// Elements in front of the 4-element groups of a vector kernel over arrays
 // `p[0..np)` of element sizes `esz` that share a phase: the distance to the
-// next common 256-, 64- or 4-element boundary (the coarsest they share),
-// -1 when they share none or an array is not aligned to its own element
-// size.  Never more than n.
+// next common 256- or 64-element boundary (the coarsest they share) when `n`
+// reaches it, else to the next 4-element one, -1 when they share none or an
+// array is not aligned to its own element size.  Never more than n.  A head of
+// four or more ends on such a boundary, so the groups it is made of are
+// aligned like the others (cut off at n they were not: a bf16 array of 6
+// elements from element 3 on had its group at element 5).
 int common_head(const void *const *p, const int *esz, int np, int64_t n)
 {
     if (np == 0)
@@ -244,26 +247,25 @@ int common_head(const void *const *p, const int *esz, int np, int64_t n)
         same64 = same64 && (e & 63) == (ph & 63);
         same4 = same4 && (e & 3) == (ph & 3);
     }
-    int64_t head;
-    if (same256)
-        head = (kTileElems - ph) % kTileElems;
-    else if (same64)
-        head = (64 - (ph & 63)) & 63;
-    else if (same4)
-        head = (4 - (ph & 3)) & 3;
-    else
+    if (!same4)
         return -1;
+    int64_t head = same256  ? (kTileElems - ph) % kTileElems
+                   : same64 ? (64 - (ph & 63)) & 63
+                            : (4 - (ph & 3)) & 3;
+    if (head > n)
+        head = (4 - (ph & 3)) & 3;
     return static_cast<int>(head < n ? head : n);
 }
 
-// Elements to do one by one before the vector kernels can take arrays that
-// share no phase (common_head found none): the reference array `p[ref]` (the
-// first output) is brought to a 256-element boundary, or to one element past
-// it when that puts every 2-byte array on a 4-byte boundary, and every other
-// array is then accessed at whatever 4-byte-aligned address it has (a group
-// access needs 4-byte alignment only).  -1 when no head does that (2-byte
-// arrays at both odd and even element offsets) or an array is not aligned
-// to its element size.  Never more than n.
+// The same for arrays that share no phase (common_head found none): the
+// reference array `p[ref]` (the first output) is brought to a 256-element
+// boundary, or to one element past it when that puts every 2-byte array on a
+// 4-byte boundary, and every other array is then accessed at whatever
+// 4-byte-aligned address it has (a group access needs 4-byte alignment only).
+// When `n` does not reach that, the 2-byte arrays' boundary is all that is
+// taken.  -1 when no head does that (2-byte arrays at both odd and even
+// element offsets) or an array is not aligned to its element size.  Never
+// more than n.
 int shifted_head(const void *const *p, const int *esz, int np, int ref, int64_t n)
 {
     for (int i = 0; i < np; ++i)
@@ -276,8 +278,11 @@ int shifted_head(const void *const *p, const int *esz, int np, int ref, int64_t 
         for (int i = 0; i < np && ok; ++i)
             ok = (reinterpret_cast<uintptr_t>(p[i]) +
                   static_cast<uintptr_t>(head) * static_cast<uintptr_t>(esz[i])) % 4 == 0;
-        if (ok)
+        if (ok) {
+            if (head > n)
+                head &= 1;  // boundaries of 4 bytes are two elements apart
             return static_cast<int>(head < n ? head : n);
+        }
     }
     return -1;
 }

@@ -424,6 +424,18 @@ void fuzz_errors(int iters)
         CHECK(disdp_status_string(static_cast<disdp_status_t>(s)) != nullptr, "status %d", s);
 }
 
+// Every 4-element group a kernel forms of a piece with `head` elements before
+// and `n` from the pointers on -- whole groups of the head up to the pointers,
+// whole groups from them on -- starts on a 4-byte boundary in every array.
+void check_groups(const void *const *ptrs, int count, int head, int64_t n)
+{
+    if (head < 4 && n < 4)
+        return;  // no group: single elements only
+    for (int i = 0; i < count; ++i)
+        CHECK(reinterpret_cast<uintptr_t>(ptrs[i]) % 4 == 0,
+              "array %d: groups off a 4-byte boundary (head %d, n %" PRId64 ")", i, head, n);
+}
+
 // ---- valid calls: which kernel, head and advanced pointers ------------------------
 void fuzz_alignment(int iters)
 {
@@ -489,8 +501,27 @@ void fuzz_alignment(int iters)
                 }
             }
         }
+        // a tensor that ends before the boundary reaches for the next 4-byte
+        // (no shared phase) or 4-element one, so that no group is cut short
+        if (want_head > n)
+            want_head = disturb == 2 ? want_head & 1 : (4 - (phase & 3)) & 3;
         if (want_head > n)
             want_head = n;
+        if (g_vec) {
+            std::vector<const void *> all = {a.p, a.m, a.v, a.p16};
+            all.insert(all.end(), a.g, a.g + W);
+            check_groups(all.data(), static_cast<int>(all.size()), a.head, a.n);
+        }
+        const disdp::LaunchArgs fused_args = g_args;
+        const bool fused_vec = g_vec;
+        CHECK(disdp_quantize(g[0], static_cast<disdp_dtype_t>(gdt), n, 24,
+                             reinterpret_cast<int32_t *>(p), nullptr) == DISDP_OK, "quantize");
+        if (g_vec) {
+            const void *const both[] = {g_qargs.g, g_qargs.out};
+            check_groups(both, 2, g_qargs.head, g_qargs.n);
+        }
+        g_args = fused_args;
+        g_vec = fused_vec;
         CHECK(g_vec == want_vec, "vec %d want %d (disturb %d phase %d)", g_vec, want_vec, disturb,
               phase);
         CHECK(a.head == want_head, "head %d want %d (disturb %d phase %d n %" PRId64 ")", a.head,
@@ -504,7 +535,7 @@ void fuzz_alignment(int iters)
                   "contribution %d not advanced by the head", w);
         if (g_vec && a.n > 0 && disturb == 2) {
             const uintptr_t pe = reinterpret_cast<uintptr_t>(a.p) / 4 % 256;
-            CHECK(pe == 0 || pe == 1, "p at element %d past a 256-element boundary",
+            CHECK(pe == 0 || pe == 1 || a.head <= 1, "p at element %d past a 256-element boundary",
                   static_cast<int>(pe));
             const void *all[] = {a.p, a.m, a.v, a.p16};
             for (const void *q : all)
@@ -513,7 +544,10 @@ void fuzz_alignment(int iters)
                 CHECK(reinterpret_cast<uintptr_t>(a.g[w]) % 4 == 0,
                       "contribution %d not on a 4-byte boundary", w);
         } else if (g_vec && a.n > 0) {
-            const int gran = disturb == 0 ? 256 : disturb == 4 ? 64 : 4;
+            const int gran = a.head < 4 && (a.n >> 2) < 64 ? 4
+                             : disturb == 0                ? 256
+                             : disturb == 4                ? 64
+                                                           : 4;
             for (int w = 0; w < W; ++w)
                 CHECK((reinterpret_cast<uintptr_t>(a.g[w]) / gb) % gran == 0,
                       "contribution %d not on a %d-element boundary", w, gran);
@@ -628,6 +662,7 @@ void fuzz_multi(int iters)
                       "tensor %d: head %d n %lld of %lld", j, h, (long long)ma.n[c], (long long)n[j]);
                 const int64_t tiles = std::max<int64_t>(1, ((ma.n[c] >> 2) + 63) / 64);
                 CHECK(ma.tile_start[c + 1] - ma.tile_start[c] == tiles, "tensor %d: tiles", j);
+                check_groups(ma.ptr + c * per, per, h, ma.n[c]);
                 for (int w = 0; w < W; ++w) {
                     const char *q = static_cast<const char *>(ma.ptr[c * per + w]);
                     CHECK(q == static_cast<const char *>(g[static_cast<size_t>(j) * W + w]) + int64_t(h) * gb,
