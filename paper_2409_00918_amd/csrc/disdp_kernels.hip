@@ -191,9 +191,12 @@ __device__ __forceinline__ void adamw(const StepScalars &s, float agg, float &p,
 // What a lane derives from the step constants while its loads are in
 // flight, for the short forms of the two divisions by a bias correction c:
 // zh = 1/c correctly rounded and zl = 1/c - zh.  `tame`: the constants lie
-// where those forms hold (see adamw4).
+// where those forms hold (see adamw4).  `zero_v`: the distance of a second
+// moment of zero from the range they hold in: 0 when eps alone can be the
+// divisor.
 struct Reciprocals {
     float zh1, zl1, zh2, zl2;
+    uint32_t zero_v;
     bool tame;
 };
 
@@ -207,13 +210,16 @@ __device__ __forceinline__ Reciprocals reciprocals(const StepScalars &s)
     // not sunk to their use behind the waits for the loads
     asm volatile("" : "+v"(r.zh1), "+v"(r.zl1), "+v"(r.zh2), "+v"(r.zl2));
     // as integers (scalar compares): a sign bit or a NaN is above the ends
-    constexpr uint32_t kLo = (127u - 24u) << 23, kOne = 127u << 23, kEps = (127u + 40u) << 23;
+    constexpr uint32_t kLo = (127u - 24u) << 23, kOne = 127u << 23;
+    constexpr uint32_t kEpsLo = (127u - 48u) << 23, kEps = (127u + 40u) << 23;
+    r.zero_v = __float_as_uint(s.eps) >= kEpsLo ? 0 : ~0u;
     r.tame = __float_as_uint(s.bc1) - kLo <= kOne - kLo &&
              __float_as_uint(s.bc2) - kLo <= kOne - kLo && __float_as_uint(s.eps) <= kEps;
     return r;
 }
 
-// x / c, correctly rounded, for 2^-24 <= c <= 1 and 2^-96 <= |x| <= 2^60.
+// x / c, correctly rounded, for 2^-24 <= c <= 1 and 2^-96 <= |x| <= 2^60 or x
+// = +0 (the quotient is +0 whatever the sign of zl; -0 would lose its sign).
 // q is x * (1/c) with 1/c held in two floats, so within 0.5 + 2^-21 units of
 // the quotient; the remainder x - q*c is then exact, and as zh is the
 // correctly rounded 1/c one more step rounds correctly (Markstein, "Computation
@@ -224,13 +230,15 @@ __device__ __forceinline__ float div_const(float x, float c, float zh, float zl)
     return __builtin_fmaf(__builtin_fmaf(-q, c, x), zh, q);
 }
 
-// sqrt(x), correctly rounded on gfx950 for 2^-100 <= x <= 2^100: one
-// correction of x * v_rsq_f32(x).  Every float of that range was compared
-// with sqrtf on MI355X (rsq is a function of the significand and the
-// exponent's parity, so that is 2^24 cases, each at every scale).
+// sqrt(x), correctly rounded on gfx950 for 2^-100 <= x <= 2^100 and +0: one
+// correction of x * v_rsq_f32(x).  The correction depends on the significand
+// and the exponent's parity only, that is 2^24 cases: tests/test_adam_range_gpu.py
+// has each of them at four scales.
 __device__ __forceinline__ float sqrt_mid(float x)
 {
-    const float y = __builtin_amdgcn_rsqf(x);
+    constexpr uint32_t kLo = (127u - 100u) << 23;
+    const uint32_t u = __float_as_uint(x);   // 1/sqrt(0) would be infinite
+    const float y = __builtin_amdgcn_rsqf(__uint_as_float(u > kLo ? u : kLo));
     const float g = x * y;
     return __builtin_fmaf(__builtin_fmaf(-g, g, x), 0.5f * y, g);
 }
@@ -247,14 +255,20 @@ __device__ __forceinline__ float div_mid(float n, float d)
 }
 
 // adamw on the four elements of a lane, the same bits in fewer instructions
-// (a W = 8 fp32 group 316 -> 215 vector instructions, 30 of them while its
+// (a W = 8 fp32 group 316 -> 239 vector instructions, 30 of them while its
 // loads are in flight).
 // The kernel is bound by memory at shard sizes, but a launch of a few
 // megabytes runs its waves in step -- all load, all compute, all store -- and
 // the arithmetic adds to its time.  The short divisions and square root need
-// the moments in a middle range (2^-60..2^20 for |m|, 2^-96..2^60 for v),
-// which gradients of trained models keep; a lane with an element outside it
-// (a zero, denormal, infinity or NaN included) takes the general form.
+// the moments in a middle range (2^-60..2^20 for |m|, 2^-96..2^60 for v) or
+// exactly zero, as those of padding, unused rows and frozen weights are; a
+// wave with an element outside it (a denormal, -0, infinity or NaN included)
+// takes the general form whole.  A branch per lane would run both forms in
+// such a wave: with 5% of the elements far, W = 8 fp32 at n = 2.5e7 took 237-242
+// us that way, 219 this way, 215 with none far (the general form for
+// all, at the occupancy it likes: 218).  Zeros in the short form cost 24
+// instructions: 215 us with 0, 5% or 100% of the elements at zero, against 214
+// and 219 (5%).
 __device__ __forceinline__ void adamw4(const StepScalars &s, const Reciprocals &r,
                                        const float (&agg)[4], float (&p)[4], float (&m)[4],
                                        float (&v)[4])
@@ -268,12 +282,14 @@ __device__ __forceinline__ void adamw4(const StepScalars &s, const Reciprocals &
         const float g = agg[e] * s.grad_scale;
         mi[e] = s.b1 * m[e] + s.omb1 * g;
         vi[e] = s.b2 * v[e] + s.omb2 * (g * g);
-        const uint32_t dm = (__float_as_uint(mi[e]) << 1) - 2 * kMLo;
-        const uint32_t dv = __float_as_uint(vi[e]) - kVLo;
+        const uint32_t um = __float_as_uint(mi[e]), uv = __float_as_uint(vi[e]);
+        const uint32_t dm = um ? (um << 1) - 2 * kMLo : 0;
+        const uint32_t dv = uv ? uv - kVLo : r.zero_v;
         far_m = dm > far_m ? dm : far_m;
         far_v = dv > far_v ? dv : far_v;
     }
-    if (__builtin_expect(r.tame && far_m <= 2 * (kMHi - kMLo) && far_v <= kVHi - kVLo, 1)) {
+    const bool mid = r.tame && far_m <= 2 * (kMHi - kMLo) && far_v <= kVHi - kVLo;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!mid) == 0, 1)) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float mh = div_const(mi[e], s.bc1, r.zh1, r.zl1);

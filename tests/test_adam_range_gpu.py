@@ -1,9 +1,9 @@
 """The optimizer's arithmetic where its short forms begin and end.
 
-Four elements of a lane take short divisions and a short square root when the
-updated moments lie in a middle range (|m| in 2^-60..2^20, v in 2^-96..2^60)
-and the step constants are ordinary ones; any other lane takes the general
-form.  Either way every bit must be the oracle's.  With beta = 0.5 and a zero
+A wave takes short divisions and a short square root when the updated moments
+of all its elements lie in a middle range (|m| in 2^-60..2^20, v in
+2^-96..2^60) or are zero, and the step constants are ordinary ones; any other
+wave takes the general form.  Either way every bit must be the oracle's.  With beta = 0.5 and a zero
 gradient the updated moments are exactly half the given ones, so both ends of
 the ranges and every significand can be hit on the spot.
 """
@@ -41,6 +41,45 @@ def test_square_root_of_every_significand(exponent):
     m = np.full(n, 2.0, np.float32)
     got, want = _step(zero, zero, m, v, 1, _hp(eps=0.0))
     assert_parity(got, want, f"exponent {exponent}")
+
+
+@pytest.mark.parametrize("exponent", [-95, -40, 1, 38])
+def test_square_root_of_every_significand_seen_exactly(exponent):
+    # the weight is -m/d with m just below the root d, so the quotient lies
+    # just below 1, where neighbouring d give quotients a unit apart or more
+    n = 1 << 24
+    v = (np.arange(n, dtype=np.uint32) + np.uint32((127 + exponent) << 23)).view(np.float32)
+    m = (np.sqrt(v.astype(np.float64)) * (1 - 2.0**-22)).astype(np.float32)
+    zero = np.zeros(n, np.float32)
+    got, want = _step(zero, zero, m, v, 1, _hp(eps=0.0))
+    assert_parity(got, want, f"exponent {exponent}")
+    root = np.sqrt(v)
+    assert np.all(m / np.nextafter(root, np.float32(0)) != m / root)
+    assert np.all(m / np.nextafter(root, np.float32(np.inf)) != m / root)
+
+
+@pytest.mark.parametrize("eps", [1e-8, 2.0**-48, np.nextafter(np.float32(2.0**-48), np.float32(0)),
+                                 0.0])
+@pytest.mark.parametrize("lr", [1e-3, -1e-3])
+@pytest.mark.parametrize("share", [1 / 64, 0.3, 1.0])
+def test_zero_moments_among_ordinary_ones(eps, lr, share):
+    # m, v or both at zero (rows that have had no gradient), alone in their
+    # wave or all of it; eps at the end of where it may divide alone and past it
+    n = 64 * 256 + 7
+    rng = np.random.default_rng(9)
+    p = rng.standard_normal(n).astype(np.float32) * np.float32(0.02)
+    p[rng.random(n) < 0.2] = 0.0
+    p[rng.random(n) < 0.1] = -0.0
+    g = rng.standard_normal(n).astype(np.float32) * np.float32(1e-4)
+    m = rng.standard_normal(n).astype(np.float32) * np.float32(1e-4)
+    v = m * m + np.float32(1e-12)
+    zm, zv = rng.random(n) < share, rng.random(n) < share
+    g[zm | zv] = np.where(rng.random(n) < 0.5, np.float32(0), np.float32(-0.0))[zm | zv]
+    m[zm], v[zv] = 0.0, 0.0
+    m[rng.random(n) < 1e-3] = -0.0
+    for beta1, beta2 in ((0.9, 0.95), (0.0, 0.0), (0.5, 0.999)):
+        got, want = _step(g, p, m, v, 3, _hp(beta1, beta2, eps, lr=lr, wd=0.1))
+        assert_parity(got, want, f"eps {eps} lr {lr} share {share} betas {beta1} {beta2}")
 
 
 @pytest.mark.parametrize("beta1,beta2,eps,t", [
