@@ -903,68 +903,99 @@ __global__ DISDP_WAVE_LAUNCH_BOUNDS void quantize_element_kernel(QuantizeArgs q)
 // Resident waves per CU, by the bytes of loads a lane keeps in flight (4
 // elements of each contribution; p, m and v with the optimizer).  What streams
 // best is the fewest waves that still cover the memory's latency: the tiles
-// in flight are then the shortest stretch of every array.  One wave more per
-// CU costs up to 3%, one fewer up to 10%, so the tables lean to the
-// higher side.  0 = as many as fit.  All figures are TB/s at n = 2e8 (run-time
-// W: 1e8), caps of 3-24 interleaved in one process; in brackets the caps next
-// to the chosen one.
+// in flight are then the shortest stretch of every array.  One wave too few
+// costs up to 14%, one too many 1-3%.  0 = as many as fit.
 //
-// Fused: fp32 W = 1 (64 B) 9: 6.78 (8: 6.68; 10: 6.70); W = 2 (80) 8: 6.77
-// (6.65; 6.66); W = 4 (112) 7: 6.79 (6.78; 6.70); W = 5 (128) 6: 6.75 (6.60;
-// 6.66); W = 6 (144) 6: 6.77 (6.77; 6.65); W = 8 (176) 5: 6.76 (6.61; 6.55);
-// W = 12, 16 (240, 304) 4: 6.57, 6.47 (5: 6.40, 6.36); bf16 W = 4, 8, 12, 16:
-// 6.69, 6.61, 6.56, 6.42 at 8, 7, 6, 5.  Fixed point converting fp32 is the
-// same (W = 4, 8: 6.73, 6.71 at 7, 5); converting bf16, twice the conversions
-// per byte, it wants one more from 112 B on (W = 8, 16: 6.55, 6.35 at 8, 6).
-// An aggregate written too wants two more (W = 8, 7 waves: 6.54 in fp32, 6.50
-// in fixed point; 5: 6.23, 6.17).
-constexpr int fused_waves(int lane_bytes, bool converts_bf16)
+// Every entry is the cap whose worst case was best, of 24 to 28: the planned
+// slab, arrays in allocations of their own, and scattered offsets, at n = 1e7,
+// 2.5e7, 5e7 and 2e8 on two cards, and with 5% of the moments far from the short
+// arithmetic's range; caps interleaved in one process.  Figures: how
+// far the time lies above the best cap's, worst / mean in percent, in
+// brackets the caps next to the chosen one.
+//
+// Fused: fp32 W = 1 (64 B) 10: 2.5 / 0.4 (9: 8.0 / 2.2; 11: 4.7 / 0.9); W = 2
+// (80) 9: 2.0 / 0.3 (8: 10.4 / 2.3; 10: 2.4 / 0.8); W = 3 (96) 8: 2.3 / 0.4 (7:
+// 3.1 / 1.7; 9: 1.9 / 0.5); W = 4 (112) 8: 2.4 / 0.6 (7: 3.3 / 0.6); W = 5, 6
+// (128, 144) 7: 3.9 / 1.1 (6: 5.8 / 1.4); W = 7, 8 (160, 176) 6: 3.9 / 0.7 (5: 9.2
+// / 2.2; 7: 5.0 / 2.1); W = 12 (240) 5: 3.8 / 0.9 (4: 4.8 / 0.9); W = 16 (304) 4:
+// 5.6 / 0.4 (5: 5.6 / 1.9); bf16 W = 2, 4, 8, 12, 16 at 10, 9, 8, 7, 6: 2.6, 2.5,
+// 4.0, 1.4, 2.0 / 0.4-0.8.
+// From kLargeElems on, float or int32 contributions that are not converted want
+// one fewer between 112 and 240 B (W = 8 on slabs of 2e8 to 9.3e8 elements 5:
+// 0.4 on average, 6: 1.2; in allocations of their own, n = 8.75e8, 6 is 1.4
+// behind; 1% on a list of 1.04e8); below it one fewer costs W = 8 up to 9 (n =
+// 5e7), and 3 with far moments.
+// Converting bf16, twice the conversions per byte, it wants one more, above 144 B
+// two (W = 2, 4, 8, 12, 16 at 11, 10, 9, 8, 8: 1.8, 4.1, 3.0, 2.1, 1.9 / 0.3-0.8; W =
+// 4 at 8: 12.2 / 6.6).  An aggregate written too wants two more (W = 8, 8 waves:
+// 1.7 / 0.2; 6: 4.5 / 2.1).
+constexpr int64_t kLargeElems = 100000000;
+constexpr int fused_waves(int lane_bytes, bool converts_bf16, bool large)
 {
-    const int waves = lane_bytes <= 64    ? 9
-                      : lane_bytes <= 80  ? 8
-                      : lane_bytes <= 112 ? 7
-                      : lane_bytes <= 144 ? 6
-                      : lane_bytes <= 176 ? 5
+    const int waves = lane_bytes <= 64    ? 10
+                      : lane_bytes <= 80  ? 9
+                      : lane_bytes <= 112 ? 8
+                      : lane_bytes <= 144 ? 7
+                      : lane_bytes <= 176 ? 6
+                      : lane_bytes <= 240 ? 5
                                           : 4;
-    return converts_bf16 && lane_bytes >= 112 ? waves + 1 : waves;
+    if (converts_bf16)
+        return waves + (lane_bytes <= 144 ? 1 : 2);
+    return large && lane_bytes >= 112 && lane_bytes <= 240 ? waves - 1 : waves;
 }
 
 // The aggregation alone reads nearly all it moves and wants more loads in
-// flight: fp32 W = 1, 2 (16, 32 B) uncapped: 6.69, 6.73 (24: 6.36, 6.68; 12:
-// 4.78, 5.43); W = 3 16: 6.63; W = 4 14: 6.54 (12: 6.47; 16: 6.36); W = 5, 6
-// 10: 6.52, 6.52; W = 8 8: 6.46 (7: 6.35; 9: 6.35); W = 12, 16 6: 6.44, 6.25;
-// bf16 W = 2, 4 uncapped: 6.70, 6.62; W = 8, 12, 16 14, 10, 8: 6.52, 6.38,
-// 6.24.  Converting bf16, W = 16 9: 6.11 (8: 6.01).
-constexpr int aggregate_waves(int lane_bytes, bool converts_bf16)
+// flight, by the same measure: fp32 W = 1, 2 (16, 32 B) uncapped: 0.5 / 0.1 (24,
+// 20: 5.9, 5.8); W = 3 18: 3.2 / 0.9; W = 4 14: 3.6 / 0.9 (12: 6.5; 16: 3.1 / 1.3);
+// W = 6 10: 2.0 / 0.4; W = 8 8: 1.2 / 0.1 (7: 4.5; 9: 1.7); W = 12, 16 6: 0.5, 1.2;
+// bf16 W = 4 uncapped 2.3 / 0.3; W = 8, 12, 16 14, 10, 9: 1.3, 1.1, 2.1.
+// Converting bf16, W = 16 11: 2.4 / 0.5 (10: 3.0 / 0.7).
+constexpr int aggregate_waves(int lane_bytes, bool bf16, bool converts_bf16)
 {
     const int waves = lane_bytes <= 32    ? 0
-                      : lane_bytes <= 48  ? 16
+                      : lane_bytes <= 48  ? 18
                       : lane_bytes <= 64  ? 14
                       : lane_bytes <= 96  ? 10
-                      : lane_bytes <= 128 ? 8
+                      : lane_bytes <= 128 ? 8 + bf16
                                           : 6;
-    return converts_bf16 && lane_bytes >= 112 ? waves + 1 : waves;
+    return converts_bf16 && lane_bytes >= 112 ? waves + 2 : waves;
 }
 
 // The run-time worker-count kernels, whose lanes keep chunks of 128 bytes in
-// flight and then smaller pieces.  Fused: fp32 W = 9, 10, 13 7: 6.54, 6.58,
-// 6.43; W = 17, 20 5: 6.29, 6.34 (6: 6.29, 6.18); W = 24, 32, 40, 64 4: 6.21,
-// 6.35, 6.09, 6.08 (5: 6.20, 6.34, 6.02, 6.02; 3: 5.6-5.9); bf16 W = 9, 13 10:
-// 6.45, 6.38; W = 20 7: 6.36; W = 24, 32, 64 6: 6.21, 6.04, 5.78 (5: 6.14,
-// 6.12, 5.82).  Fixed point converting fp32 the same but 5 from W = 16 on (W =
-// 24, 64: 6.25, 6.02; 4: 5.92, 5.84), converting bf16 two or three more (W =
-// 24, 32, 64 at 8, 9, 9: 6.22, 6.07, 6.03).  The aggregation alone: fp32 W = 9
-// 9: 6.48; W = 24, 32, 64 6: 6.15, 6.13, 6.14-6.39; bf16 W = 10 14: 6.19; W = 24
-// 9: 6.11; W = 32, 64 8: 6.04, 6.03.
+// flight and then the smaller pieces of the remainder, one after another: the more
+// pieces, the more waves.  By the same measure (worst / mean).
+// Fused bf16: W = 9, 11, 13, 15 11, 12, 12, 13: 1.7, 2.7, 1.9, 2.1 (10 for all: 3.2,
+// 8.5, 6.5, 9.4); W = 17, 19, 23, 24, 28, 31 9, 10, 11, 7, 9, 11: 3.0, 1.1, 0.6, 1.0, 2.2,
+// 1.8 (7 for all: 7.1, 9.9, 10.5, 1.0, 3.4, 10.4); W = 33, 39, 47, 63, 64 8, 9, 9, 9, 7:
+// 0.9, 0.1, 0.2, 0.8, 1.3.  Converting: W = 9, 11, 15 1.4, 2.1, 1.5; W = 17, 19, 23, 24,
+// 31, 39 10, 11, 12, 9, 12, 11: 1.2, 1.9, 0.8, 0.9, 0.2, 0.7.
+// Fused fp32: W = 9, 11, 15 8: 1.3, 0.7, 1.0; W = 17, 20, 23 6, 5, 7: 1.4, 0.9, 1.3; W
+// = 24, 27, 31 4, 6, 6: 0.6, 2.1, 1.3 (4 for all: 0.6, 8.6, 11.4); W = 33, 47, 63, 64 5, 5,
+// 5, 4: 0.7, 0.7, 3.8, 4.3.  Converting: W = 9, 15 8: 3.3, 1.4; W = 19, 23, 24, 31, 63 7,
+// 7, 5, 7, 6: 1.6, 1.4, 2.1, 0.7, 2.6.
+// The aggregation alone, bf16: W = 9, 15 16: 0.6, 0.5; W = 17, 20, 23 12, 12, 14: 1.1,
+// 2.1, 0.2; W = 24, 31, 33, 39, 64 9, 13, 10, 11, 9: 1.1, 1.5, 0.9, 0.5, 2.4; fp32: W = 9,
+// 15 9: 1.5, 1.5; W = 17, 23 7: 1.0, 2.6; W = 24, 31 6: 2.4, 1.1; W = 32, 64 5: 1.1, 1.7.
 int runtime_w_waves(int W, int gt, int mode, bool adam)
 {
-    const bool bf16 = gt == kGradBF16;
     const bool converts = mode == kAggFixed && gt != kGradI32;
+    if (gt == kGradBF16) {
+        const int pieces = __builtin_popcount(W & 7);   // of fewer than 8
+        if (W < 16)
+            return adam ? 9 + __builtin_popcount(W) : 16;
+        if (!adam)
+            return (pieces == 0 ? 9 : W >= 32 ? 9 + (pieces + 1) / 2 : 10 + pieces + (W < 24)) +
+                   2 * converts;
+        if (W >= 32 || pieces == 0)
+            return 7 + (pieces + 1) / 2 + 2 * converts;
+        return 8 + pieces + converts;
+    }
     if (!adam)
-        return bf16 ? (W < 16 ? 14 : W < 32 ? 9 : 8) : W < 16 ? 9 : 6;
-    if (bf16)
-        return (W < 16 ? 10 : W < 24 ? 7 : 6) + (converts ? (W < 32 ? 2 : 3) : 0);
-    return W < 16 ? 7 : W < 24 || converts ? 5 : 4;
+        return W < 16 ? 9 : W < 24 ? 7 : W < 32 ? 6 : 5;
+    if (W < 16)
+        return 8;
+    const int pieces = __builtin_popcount(W & 3);       // of fewer than 4
+    return (W < 24 || converts ? 5 : 4) + (W < 32 ? pieces : pieces > 0);
 }
 
 // The caps above pay once a launch is many rounds of resident waves; one of a
@@ -1156,6 +1187,36 @@ void advance(VectorArgs<W> &k, int64_t elems, int grad_bytes)
         k.g[w] += elems * grad_bytes;
 }
 
+// Whether the contributions lie `step` bytes or a multiple of it apart, give or
+// take 4 MiB: any two neighbours of them, or every two.
+bool multiples_apart(const LaunchArgs &a, uintptr_t step, bool every)
+{
+    constexpr uintptr_t kNear = uintptr_t(4) << 20;
+    for (int w = 1; w < a.W; ++w) {
+        const uintptr_t apart = reinterpret_cast<uintptr_t>(a.g[w]) -
+                                reinterpret_cast<uintptr_t>(a.g[w - 1]);
+        if (((apart + kNear) % step <= 2 * kNear) != every)
+            return !every;
+    }
+    return every;
+}
+
+// Waves for the fused kernels of 7 to 16 four-byte contributions that lie a
+// multiple of 256 MiB apart (a flat buffer of 2^26 or 2^27 elements each, the planned
+// slab at 5.0e7 to 5.8e7), where the same tile of every array falls to the
+// same channels.  Against the table's caps: W = 8, 12, 16 at n = 2^26 0.3, 4.5, 8.0%
+// faster, 2^27 1.8, 1.5, 3.0%, the slab at 5e7 0.5, 2.5, 4.5%; from 1 GiB apart on it
+// loses as often (n = 2^28: 1.8, 3.9, -4.5%).
+constexpr int kSameChannelWaves = 8;
+bool same_channels(const LaunchArgs &a)
+{
+    constexpr uintptr_t kMiB = uintptr_t(1) << 20;
+    const uintptr_t first = reinterpret_cast<uintptr_t>(a.g[0]);
+    const uintptr_t second = reinterpret_cast<uintptr_t>(a.g[a.W > 1 ? 1 : 0]);
+    const uintptr_t apart = first < second ? second - first : first - second;
+    return apart >= 128 * kMiB && apart < 896 * kMiB && multiples_apart(a, 256 * kMiB, true);
+}
+
 // Tiles in a row that one XCD takes, as a log2: 1 for large launches over many
 // bf16 contributions.  A bf16 tile is 512 bytes of each; two neighbours on one
 // XCD make a 1 KiB read of it, as one fp32 tile is (together / one by one, each
@@ -1174,27 +1235,10 @@ void advance(VectorArgs<W> &k, int64_t elems, int grad_bytes)
 int tiles_together(const LaunchArgs &a, bool adam, int base_waves)
 {
     constexpr int kRounds = 16;
-    constexpr uintptr_t kRepeat = uintptr_t(64) << 20, kNear = uintptr_t(4) << 20;
     if (a.gdtype != kGradBF16 || a.W < (adam ? 12 : 16) ||
         ceil_div(a.n >> 2, kWave) <= int64_t(kRounds) * base_waves * cu_count())
         return 0;
-    for (int w = 1; w < a.W; ++w) {
-        const uintptr_t apart = reinterpret_cast<uintptr_t>(a.g[w]) -
-                                reinterpret_cast<uintptr_t>(a.g[w - 1]);
-        if ((apart + kNear) % kRepeat <= 2 * kNear)
-            return 0;
-    }
-    return 1;
-}
-
-// The caps of such launches, which are flatter: fused W = 16 at 6, 7, 8, 10:
-// 6.60, 6.57, 6.52, 6.48 (fixed point at 7, 8, 10: 6.50, 6.51, 6.45; W = 64 at
-// 6, 9, 11: 5.37, 5.99, 6.01); the aggregation of 64 in fixed point at 7, 9, 11:
-// 5.94, 6.17, 6.10.
-constexpr int together_waves(int W, bool adam, bool converts)
-{
-    return adam ? (W <= 16 ? 7 : W < 32 ? 8 : W < 48 ? 7 : 6) + (!converts ? 0 : W <= 16 ? 1 : 3)
-                : (W < 32 ? 9 : 7) + 2 * converts;
+    return multiples_apart(a, uintptr_t(64) << 20, false) ? 0 : 1;
 }
 
 template <int W, int GT, int MODE, bool ADAM>
@@ -1210,11 +1254,13 @@ hipError_t launch_vector(const LaunchArgs &a, Shape shape, hipStream_t stream)
         base = shared_waves(ADAM, kConverts);
     } else {
         base = W == 0 ? runtime_w_waves(a.W, GT, MODE, ADAM)
-               : ADAM ? fused_waves(kLaneBytes, kConverts && GT == kGradBF16)
-                      : aggregate_waves(kLaneBytes, kConverts && GT == kGradBF16);
+               : ADAM ? fused_waves(kLaneBytes, kConverts && GT == kGradBF16,
+                                    GT != kGradBF16 && !kConverts && a.n >= kLargeElems)
+                      : aggregate_waves(kLaneBytes, GT == kGradBF16,
+                                        kConverts && GT == kGradBF16);
+        if (ADAM && W >= 7 && kGradBytes == 4 && base < kSameChannelWaves && same_channels(a))
+            base = kSameChannelWaves;
         together = tiles_together(a, ADAM, base);
-        if (together)
-            base = together_waves(a.W, ADAM, kConverts);
         if (ADAM && (a.agg_f32 || a.agg_i32))
             base += 2;
         if (ceil_div(a.n >> 2, kWave) <= int64_t(kUncappedRounds) * base * cu_count())
@@ -1359,11 +1405,11 @@ hipError_t launch_multi_w(const MultiArgs &a, hipStream_t stream)
     constexpr int kGradBytes = GT == kGradBF16 ? 2 : 4;
     constexpr int kLaneBytes = W > 0 ? 4 * (W * kGradBytes + 12) : 1 << 30;
     constexpr bool kConverts = MODE == kAggFixed && GT != kGradI32;
-    // two waves more than one tensor's kernel: they look their tensor up
+    // one wave more than one tensor's kernel: they look their tensor up
     // before their loads (122 tensors of 15.7M elements, W = 4 bf16, 10 waves
     // 87.3 us, 8 89.8, 12 88.1)
-    const int base = 2 + (W == 0 ? runtime_w_waves(a.W, GT, MODE, true)
-                                 : fused_waves(kLaneBytes, kConverts && GT == kGradBF16));
+    const int base = 1 + (W == 0 ? runtime_w_waves(a.W, GT, MODE, true)
+                                 : fused_waves(kLaneBytes, kConverts && GT == kGradBF16, false));
     const int lds = occupancy_lds_bytes(blocks_per_cu_cap(base, kWave, stream));
     const int per = a.W + 4;
     int general = 1;  // tensors a launch holds with rows of their own
