@@ -1226,16 +1226,20 @@ bool same_channels(const LaunchArgs &a)
 // aggregation alone W = 16, 24, 32, 64 6.39 / 6.32, 6.27 / 6.10, 6.29 / 6.05,
 // 6.06 / 5.88; fixed point, fused W = 16 6.51 / 6.35.  Fewer contributions
 // gain under 1% or lose (W = 4, 8; the aggregation of 4 and 8: -2%), a launch
-// of a few rounds loses (fused W = 16, n = 4e6 -1.5%, 1e6 -5%), fp32 too (W =
-// 1, 4, 8: -1%, -1%, -2%).  It also loses when the arrays lie a multiple of 64
+// of a few rounds loses (fused W = 16, n = 4e6 -1.5%, 1e6 -5%; at 17 rounds, the
+// aggregation of 16 at n = 1e7, -5%, at 22, n = 1.3e7, 4% ahead), fp32 too (W =
+// 1, 4, 8: -1%, -1%, -2%).  Above 7e8 elements it pays on one slab and loses on
+// allocations of their own: W = 16 at 8e8 0 and -10%, 1e9 +2 and -3%, 2e9 -2 and
+// -1%; W = 12 -9% at 8e8, W = 32 -7% at 1.25e9; at 6e8 it gains 1-4% on both.  It also loses when the arrays lie a multiple of 64
 // MiB apart, where the same tile of every array falls to the same channels:
 // fused W = 16, arrays 128 and 256 pages of 2 MiB apart 5.2 / 6.2 and 5.1 /
 // 6.3, 127 and 129 pages 5.4 / 6.2 and 4.9 / 6.2, 32 pages 6.2 / 6.3 (4 and
 // 8 tiles together did not do better over the layouts).
 int tiles_together(const LaunchArgs &a, bool adam, int base_waves)
 {
-    constexpr int kRounds = 16;
-    if (a.gdtype != kGradBF16 || a.W < (adam ? 12 : 16) ||
+    constexpr int kRounds = 20;
+    constexpr int64_t kMostElems = 700000000;
+    if (a.gdtype != kGradBF16 || a.W < (adam ? 12 : 16) || a.n > kMostElems ||
         ceil_div(a.n >> 2, kWave) <= int64_t(kRounds) * base_waves * cu_count())
         return 0;
     return multiples_apart(a, uintptr_t(64) << 20, false) ? 0 : 1;

@@ -5,7 +5,10 @@ calls build() after the library):
               include/disdp.h with the system HIP runtime and no PyTorch;
   api_fuzz    the C-ABI front end (disdp_api.cpp) compiled with g++ under
               AddressSanitizer and UndefinedBehaviorSanitizer, host code
-              only, with stub HIP calls, fuzzed without a GPU."""
+              only, with stub HIP calls, fuzzed without a GPU;
+  launch_check
+              the host code of the kernels' file, with stub HIP calls, its
+              launches checked without a GPU."""
 from __future__ import annotations
 
 import os
@@ -39,6 +42,27 @@ def build_fuzz(verbose: bool = False) -> str:
     return FUZZ_EXE
 
 
+LAUNCH_SRC = os.path.join(HERE, "launch_check.cpp")
+LAUNCH_EXE = os.path.join(HERE, "launch_check")
+
+
+def build_launch_check(verbose: bool = False) -> str:
+    """Host code only, linked without the HIP runtime (its calls are stubs)."""
+    obj, tmp = LAUNCH_EXE + ".o", LAUNCH_EXE + ".tmp"
+    cmds = [[HIPCC, "-std=c++17", "-O1", "-fPIC", "-Wall", "-Wno-unused-function",
+             "-Wno-unused-command-line-argument", "-x", "hip", "--offload-arch=gfx950",
+             "--cuda-host-only", "-fuse-cuid=none", "-I", os.path.join(ROOT, "include"),
+             "-I", os.path.join(PKG, "csrc"), "-c", "-o", obj, LAUNCH_SRC],
+            ["g++", "-o", tmp, obj]]
+    for cmd in cmds:
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.check_call(cmd)
+    os.remove(obj)
+    os.replace(tmp, LAUNCH_EXE)
+    return LAUNCH_EXE
+
+
 def build(verbose: bool = False) -> str:
     tmp = EXE + ".tmp"
     cmd = [HIPCC, "-O2", "-std=c++17", "-Wall", "-Wno-unused-command-line-argument",
@@ -50,6 +74,7 @@ def build(verbose: bool = False) -> str:
     subprocess.check_call(cmd)
     os.replace(tmp, EXE)
     build_fuzz(verbose)
+    build_launch_check(verbose)
     return EXE
 
 

@@ -55,3 +55,15 @@ def test_api_front_end_fuzz_under_sanitizers():
     r = subprocess.run([FUZZ], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-3000:]
     assert "api_fuzz: ok" in r.stdout
+
+
+def test_launches_cover_every_element_once():
+    """CPU: the host code of the kernels' file with a stub runtime: grids,
+    pieces of arrays larger than a grid, the tables of many-tensor launches,
+    and which calls give an XCD two tiles together."""
+    exe = os.path.join(HERE, "native", "launch_check")
+    if not os.path.exists(exe):
+        pytest.fail(f"{exe} is not built (python tests/native/build.py)")
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-3000:]
+    assert "launch_check: ok" in r.stdout
