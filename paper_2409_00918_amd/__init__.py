@@ -140,18 +140,28 @@ _AGGREGATE, _ADAM_STEP, _FUSED, _FUSED_DEV, _QUANTIZE = range(5)
 
 def _bind(L: ctypes.CDLL, torch) -> None:
     """Gives the native half of the binding the library's functions, and makes
-    it the way calls in the ordinary form take."""
+    it the way calls in the ordinary form take.  Without it (not built, or
+    built for another torch) the Python code below takes every call, at some
+    8 us more each."""
     global _call
-    if not os.path.exists(_BINDING_PATH):
-        raise RuntimeError(f"{_BINDING_PATH} is missing: build it with "
-                           "`python -m paper_2409_00918_amd.build`")
-    from . import _binding
+    try:
+        from . import _binding
+    except ImportError as e:
+        import warnings
+        warnings.warn(f"{_BINDING_PATH} does not load ({e}); every call goes through Python.  "
+                      "Build it with `python -m paper_2409_00918_amd.build`", RuntimeWarning)
+        _call = _left_to_python
+        return
     _binding.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.disdp_aggregate, L.disdp_adam_step, L.disdp_aggregate_adam,
         L.disdp_aggregate_adam_dev, L.disdp_quantize)),
         getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device,
         getattr(torch._C, "_cuda_getCurrentRawStream", None) or _current_stream_handle)
     _call = _binding.call
+
+
+def _left_to_python(*args) -> int:
+    return -1
 
 
 def _call(*args) -> int:

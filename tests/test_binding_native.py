@@ -1,6 +1,10 @@
 """The native half of the binding: it takes calls in the ordinary form and
 leaves every other to the Python code, without having done anything.  On the
 GPU, both ways must give the same bits and the same errors."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -49,6 +53,31 @@ def test_odd_arguments_are_left_to_python():
         dd.aggregate([torch.zeros(8)], mode="float", agg_out_f32=torch.zeros(8))
 
 
+def test_without_the_native_half_python_takes_every_call():
+    code = """
+import sys, warnings
+sys.modules["paper_2409_00918_amd._binding"] = None      # an import of it fails
+import torch
+import paper_2409_00918_amd as dd
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    assert dd.status_string(0) == "ok"
+assert any("_binding" in str(w.message) for w in seen), seen
+assert dd.raw_aggregate([0], 1, dd.DT_F32, 0, dd.AGG_FP32, 0, 0, 0, 0) == dd.OK
+assert dd._call(dd._AGGREGATE, [torch.zeros(8)]) == -1
+try:
+    dd.aggregate([torch.zeros(8)], agg_out_f32=torch.zeros(8))
+except ValueError as e:
+    assert "device tensor" in str(e)
+else:
+    raise AssertionError("a host tensor was taken")
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True,
+                       timeout=120)
+    assert r.returncode == 0, r.stderr
+
+
 def _tensors(n, W, gdtype):
     gen = torch.Generator(device="cuda").manual_seed(n + W)
     def r(scale):
@@ -65,7 +94,14 @@ def _tensors(n, W, gdtype):
 @pytest.mark.parametrize("n", [1, 4099])
 @pytest.mark.parametrize("gdtype,mode", [("f32", "fp32"), ("bf16", "fp32"), ("f32", "fixed"),
                                          ("i32", "fixed")])
-def test_both_ways_give_the_same_bits(n, gdtype, mode):
+def test_both_ways_give_the_same_bits(n, gdtype, mode, monkeypatch):
+    dd.lib()
+    native, taken = dd._call, []
+    def call(op, *args):
+        st = native(op, *args)
+        taken.append((op, st))
+        return st
+    monkeypatch.setattr(dd, "_call", call)
     g, p, m, v = _tensors(n, 3, gdtype)
     sc = torch.frombuffer(bytearray(dd.step_scalars(**KW)), dtype=torch.float32).cuda()
     here = torch.cuda.current_stream()               # an explicit stream: the Python way
@@ -94,6 +130,27 @@ def test_both_ways_give_the_same_bits(n, gdtype, mode):
                     if x is not None]
         got.append(out)
     assert got[0] == got[1]
+    # the native half took every call without a stream, none of the others saw it
+    ops = [dd._FUSED, dd._FUSED_DEV, dd._ADAM_STEP, dd._AGGREGATE]
+    ops += [dd._QUANTIZE] if gdtype != "i32" else []
+    assert taken == [(op, dd.OK) for op in ops]
+
+
+@pytest.mark.gpu
+def test_pinned_memory_is_left_to_python(monkeypatch):
+    dd.lib()
+    native, taken = dd._call, []
+    monkeypatch.setattr(dd, "_call", lambda *a: taken.append(native(*a)) or taken[-1])
+    g, p, m, v = _tensors(4096, 2, "f32")
+    want = [p.clone(), m.clone(), v.clone()]
+    dd.aggregate_adam(g, *want, None, **KW)
+    host = torch.empty(4096, pin_memory=True)
+    host.copy_(m)
+    torch.cuda.synchronize()
+    dd.aggregate_adam(g, p, host, v, None, **KW)
+    torch.cuda.synchronize()
+    assert taken == [dd.OK, -1]
+    assert torch.equal(p, want[0]) and torch.equal(host, want[1].cpu()) and torch.equal(v, want[2])
 
 
 @pytest.mark.gpu
