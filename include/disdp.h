@@ -264,8 +264,8 @@ disdp_status_t disdp_aggregate_adam_dev(const void *const *grads, int W,
 /* disdp_aggregate_adam over T tensors of one optimizer step (Section III-D,
  * step 5, applied tensor by tensor): for a shard whose tensors live in
  * separate buffers, one launch serves a batch of tensors instead of one
- * launch each (as many as 4 KiB of kernel arguments describe: 38 tensors
- * with W = 8, or some 230 when they lie at one element offset in every array, as
+ * launch each (as many as 4 KiB of kernel arguments describe: 36 tensors
+ * with W = 8, or 232 when they lie at one element offset in every array, as
  * slices of flat buffers do; tensors that follow one another without a gap
  * in every array are run as one).  Equal, bit for bit, to T
  * disdp_aggregate_adam calls with the same hyperparameters.

@@ -392,8 +392,8 @@ disdp_status_t run(const void *const *grads, int W, int gdtype, int64_t n,
     // Vector kernels move 4 elements per lane: 16-byte groups of 4-byte
     // arrays, 8-byte groups of 2-byte arrays.  Arrays that all start the same
     // number of elements past such a boundary (a sub-range of aligned arrays)
-    // take the vector kernel too: their first elements are done one by one
-    // and the pointers advanced.  When the arrays agree modulo 256 (or 64)
+    // take the vector kernel too: the pointers are advanced past their first
+    // elements, which are dealt out beside the rest.  When the arrays agree modulo 256 (or 64)
     // elements the pointers are advanced to such a boundary, which starts
     // every tile on a 1 KiB boundary (or at least every wave's stores on
     // whole cache lines), as for aligned arrays.  Arrays with unrelated
@@ -619,7 +619,6 @@ disdp_status_t disdp_aggregate_adam_multi(const void *const *grads, int W,
     disdp::MultiArgs ma;
     ma.count = 0;
     ma.s = disdp::StepScalars{};
-    ma.tile_start[0] = 0;
     ma.W = W;
     ma.gdtype = gdtype;
     ma.mode = mode;
@@ -703,10 +702,6 @@ disdp_status_t disdp_aggregate_adam_multi(const void *const *grads, int W,
         slot[W + 3] = p16 ? p16 + head : nullptr;
         ma.n[c] = len - head;
         ma.head[c] = head;
-        const int64_t groups = ma.n[c] >> 2;
-        const int64_t tiles =
-            std::max<int64_t>(1, (groups + disdp::kMultiTileGroups - 1) / disdp::kMultiTileGroups);
-        ma.tile_start[c + 1] = ma.tile_start[c] + tiles;
         ma.count = c + 1;
     }
     return flush() ? DISDP_OK : DISDP_ERR_HIP;
@@ -736,7 +731,7 @@ disdp_status_t disdp_quantize(const void *grad, disdp_dtype_t gdtype, int64_t n,
     q.head = 0;
     q.gdtype = gdtype;
     q.qscale = std::ldexp(1.0f, frac_bits);
-    // as in run(): a misalignment is peeled off one element at a time
+    // as in run(): the pointers are advanced to a common boundary
     const int gb = grad_bytes(gdtype);
     const void *ptrs[2] = {grad, out};
     const int sizes[2] = {gb, 4};

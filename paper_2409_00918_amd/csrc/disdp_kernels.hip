@@ -750,7 +750,7 @@ __global__ DISDP_LAUNCH_BOUNDS void element_kernel(VectorArgs<0> k, int64_t n)
 // flat buffers) their 64-bit element offsets and one row for all.  The whole
 // stays within 4 KiB of kernel arguments.
 constexpr int kMultiTable = 3840;
-constexpr int kMultiMost = 240;  // tensors a launch can hold (flat, 16 bytes each)
+constexpr int kMultiMost = 240;  // above what the table holds (flat, 16 bytes a tensor)
 struct MultiLaunch {
     uint32_t coarse[16];
     int count, W, rows_at, flat;
@@ -843,7 +843,7 @@ __global__ DISDP_WAVE_LAUNCH_BOUNDS void multi_kernel(MultiLaunch k)
 // single elements are dealt out by the blocks in front, as in vector_kernel.  A
 // lane has one load only, so the time between a wave's start and that load
 // counts: with the general deal() for every tile the 13B/16 contribution took
-// 743 us, this way 728 (two or four tiles a wave: 775, 793).
+// 743 us, this way 722 (two or four tiles a wave: 775, 793).
 struct QuantizeVectorArgs {
     Base g, out;
     int64_t n_groups;
@@ -1391,16 +1391,23 @@ bool same_offset(const MultiArgs &a, int base, int c, int grad_bytes)
 }
 
 // Bytes of a MultiLaunch table: first blocks, shapes, then the rows.
-int multi_slots(int count) { return (count + 1 + 15) & ~15; }
-int multi_rows_at(int count) { return (4 * (multi_slots(count) + count) + 7) & ~7; }
-int multi_bytes(int count, int W, bool flat)
+constexpr int multi_slots(int count) { return (count + 1 + 15) & ~15; }
+constexpr int multi_rows_at(int count) { return (4 * (multi_slots(count) + count) + 7) & ~7; }
+constexpr int multi_bytes(int count, int W, bool flat)
 {
     return multi_rows_at(count) + (flat ? 8 * count + 8 * (W + 4) : 8 * (W + 4) * count);
 }
 
+// what include/disdp.h states for W = 8
+static_assert(multi_bytes(36, 8, false) <= kMultiTable && multi_bytes(37, 8, false) > kMultiTable &&
+                  multi_bytes(232, 8, true) <= kMultiTable &&
+                  multi_bytes(233, 8, true) > kMultiTable &&
+                  multi_bytes(kMultiMost, 1, true) > kMultiTable,
+              "tensors of a launch");
+
 // The many-tensor kernel always runs one-wave blocks.  A launch takes the
 // next tensors that fit its arguments: as slices of flat buffers when at
-// least as many in a row are (230 against 38 tensors with rows of their own at
+// least as many in a row are (232 against 36 tensors with rows of their own at
 // W = 8), and a tensor that is alone goes to the vector kernel, which has no
 // tensor to look up.
 template <int W, int GT, int MODE>

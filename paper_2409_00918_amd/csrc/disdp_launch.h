@@ -30,8 +30,8 @@ struct LaunchArgs {
     float *agg_f32;        // optional fp32 aggregate
     int32_t *agg_i32;      // optional int32 aggregate (fixed mode)
     int64_t n;             // elements from the pointers on
-    int head;              // 0-255 elements just before the pointers, done one
-                           // by one (the pointers advanced past them)
+    int head;              // 0-255 elements just before the pointers (which were
+                           // advanced past them)
     int W, gdtype, mode, frac_bits;
     float qscale, dqscale; // 2^k and 2^-k (fixed mode)
     StepScalars s;
@@ -45,19 +45,16 @@ struct LaunchArgs {
 hipError_t launch(const LaunchArgs &a, Kind kind, bool vector_path,
                   hipStream_t stream);
 
-// Several tensors of one optimizer step: tensor c has 256-element tiles
-// tile_start[c] .. tile_start[c + 1] - 1 of the list.  launch_multi packs the
-// list into as many launches as their arguments need.
+// Several tensors of one optimizer step.  launch_multi packs the list into as
+// many launches as their arguments need.
 constexpr int kMultiMaxTensors = 240;
 constexpr int kMultiMaxPtrs = 4800;
-constexpr int kMultiTileGroups = 64;  // 4-element groups per tile
 struct MultiArgs {
     int count;                                  // tensors (>= 1)
     int W, gdtype, mode, frac_bits;
     float qscale, dqscale;                      // 2^k and 2^-k (fixed mode)
     StepScalars s;
     const StepScalars *s_dev;                   // as in LaunchArgs
-    int64_t tile_start[kMultiMaxTensors + 1];   // [count] = tiles in all
     int64_t n[kMultiMaxTensors];                // elements from the pointers on
     int head[kMultiMaxTensors];                 // 0-255 elements before them
     void *ptr[kMultiMaxPtrs];                   // tensor c at c * (W + 4): the W

@@ -9,11 +9,11 @@
 //   * each entry point with exactly one argument error injected into an
 //     otherwise valid call: the documented status, and no launch (valid
 //     fused calls: the step constants passed by value, or by address only);
-//   * disdp_aggregate_adam_multi over random tensor lists: batch packing,
-//     per-tensor heads and pointers, the single-tensor fallback, injected
-//     errors;
+//   * disdp_aggregate_adam_multi over random tensor lists: which tensors are
+//     run as one, batch packing, heads and pointers, the single-tensor
+//     fallback, injected errors;
 //   * valid calls whose arrays share, or do not share, a misalignment: the
-//     vector/element choice, the head of elements done one by one and the
+//     vector/element choice, the head of elements before the groups and the
 //     advanced pointers (on a common boundary, or every array on a 4-byte
 //     boundary with the first output on a 64-element one).
 //
@@ -560,10 +560,11 @@ void fuzz_alignment(int iters)
 
 // ---- many tensors in one call ------------------------------------------------
 // Random tensor lists (sizes, worker counts, per-tensor phases, some tensors
-// empty, some with an element-misaligned array): every non-empty tensor must
-// be launched exactly once, either in one batch slot -- with its head, its
-// pointers advanced by the head onto 4-byte boundaries, its tile range
-// ceil((n - head) / 4 / 64) (at least 1) -- or, when no head fits, on its own
+// empty, some with an element-misaligned array, some right behind the one
+// before in every array or in all but one): tensors that follow one another in
+// every array must be run as one, and every such run be launched exactly once,
+// either in one batch slot -- with its head and its pointers advanced by the
+// head, its groups on 4-byte boundaries -- or, when no head fits, on its own
 // through the element kernel; batches within their capacity.  Then one
 // error per call: an output overlapping a buffer of another tensor, a NULL
 // pointer, a bad count.
@@ -584,8 +585,38 @@ void fuzz_multi(int iters)
         std::vector<bool> odd(T, false);
         const bool copies = below(4) != 0;
         int64_t slot = 0;
+        // runs of tensors: the first of each, and its length
+        std::vector<int> run_first;
+        std::vector<int64_t> run_n;
+        const int joined = static_cast<int>(below(3));   // none, some, most
+        int last = -1;                                   // the last that is not empty
         for (int j = 0; j < T; ++j) {
             n[j] = below(5) == 0 ? 0 : below(3) == 0 ? below(300) : below(1 << 20);
+            if (last >= 0 && n[j] > 0 && below(4) < 2 * joined - 1) {
+                // right behind it; in some, one array (or the copy) is not
+                const int apart = below(3) ? -1 : static_cast<int>(below(W + 4));
+                for (int w = 0; w < W; ++w)
+                    g[static_cast<size_t>(j) * W + w] =
+                        static_cast<const char *>(g[static_cast<size_t>(last) * W + w]) +
+                        (n[last] + (apart == w ? 4 : 0)) * gb;
+                p[j] = p[last] + n[last] + (apart == W ? 4 : 0);
+                m[j] = m[last] + n[last] + (apart == W + 1 ? 4 : 0);
+                v[j] = v[last] + n[last] + (apart == W + 2 ? 4 : 0);
+                p16[j] = p16[last] ? p16[last] + n[last] : nullptr;
+                if (apart == W + 3)
+                    p16[j] = p16[last] ? (below(2) ? p16[j] + 4 : nullptr)
+                             : copies  ? reinterpret_cast<uint16_t *>(addr(slot++))
+                                       : nullptr;
+                odd[j] = odd[last];
+                if (apart < 0 || (apart == W + 3 && !copies)) {
+                    run_n.back() += n[j];
+                } else {
+                    run_first.push_back(j);
+                    run_n.push_back(n[j]);
+                }
+                last = j;
+                continue;
+            }
             const int64_t phase = below(3) ? below(512) : 0;
             const bool unrelated = below(4) == 0;
             odd[j] = below(16) == 0;
@@ -597,7 +628,13 @@ void fuzz_multi(int iters)
             v[j] = reinterpret_cast<float *>(addr(slot++) + 4 * phase);
             p16[j] = copies && below(8) ? reinterpret_cast<uint16_t *>(addr(slot++) + 2 * phase)
                                         : nullptr;
+            if (n[j] > 0) {
+                run_first.push_back(j);
+                run_n.push_back(n[j]);
+                last = j;
+            }
         }
+        const int runs = static_cast<int>(run_first.size());
         const disdp_adamw_hparams_t hp = {1e-4f, 0.9f, 0.95f, 1e-8f, 0.1f, 1 + below(1000), 1.0f};
         // the step's constants by value, or in (fake) device memory
         const bool dev = below(2) != 0;
@@ -640,28 +677,28 @@ void fuzz_multi(int iters)
               g_queries - queries, allocs.size(), g_singles.size());
         const int per = W + 4;
         const int cap = std::min(disdp::kMultiMaxTensors, disdp::kMultiMaxPtrs / per);
-        std::vector<int> seen(T, 0);
+        std::vector<int> seen(runs, 0);
         for (const disdp::MultiArgs &ma : g_multis) {
             CHECK(ma.count >= 1 && ma.count <= cap, "batch of %d tensors (cap %d)", ma.count, cap);
-            CHECK(ma.W == W && ma.tile_start[0] == 0, "batch header");
+            CHECK(ma.W == W, "batch header");
             CHECK(dev ? (ma.s_dev == reinterpret_cast<const disdp::StepScalars *>(sc) && ma.s.b1 == 0.0f)
                       : (!ma.s_dev && ma.s.b1 == hp.beta1),
                   "batch step constants");
             for (int c = 0; c < ma.count; ++c) {
                 const char *pp = static_cast<const char *>(ma.ptr[c * per + W]);
                 const int h = ma.head[c];
-                int j = -1;
-                for (int k = 0; k < T; ++k)
-                    if (n[k] > 0 && reinterpret_cast<const char *>(p[k]) + int64_t(h) * 4 == pp)
-                        j = k;
-                CHECK(j >= 0, "batch slot %d matches no tensor", c);
-                if (j < 0)
+                int r = -1;
+                for (int k = 0; k < runs; ++k)
+                    if (reinterpret_cast<const char *>(p[run_first[k]]) + int64_t(h) * 4 == pp)
+                        r = k;
+                CHECK(r >= 0, "batch slot %d matches no run of tensors", c);
+                if (r < 0)
                     continue;
-                ++seen[j];
-                CHECK(h >= 0 && h <= 255 && h <= n[j] && ma.n[c] + h == n[j],
-                      "tensor %d: head %d n %lld of %lld", j, h, (long long)ma.n[c], (long long)n[j]);
-                const int64_t tiles = std::max<int64_t>(1, ((ma.n[c] >> 2) + 63) / 64);
-                CHECK(ma.tile_start[c + 1] - ma.tile_start[c] == tiles, "tensor %d: tiles", j);
+                ++seen[r];
+                const int j = run_first[r];
+                CHECK(h >= 0 && h <= 255 && h <= run_n[r] && ma.n[c] + h == run_n[r],
+                      "tensor %d: head %d n %lld of %lld", j, h, (long long)ma.n[c],
+                      (long long)run_n[r]);
                 check_groups(ma.ptr + c * per, per, h, ma.n[c]);
                 for (int w = 0; w < W; ++w) {
                     const char *q = static_cast<const char *>(ma.ptr[c * per + w]);
@@ -679,19 +716,19 @@ void fuzz_multi(int iters)
         }
         for (size_t i = 0; i < g_singles.size(); ++i) {
             const disdp::LaunchArgs &a = g_singles[i];
-            int j = -1;
-            for (int k = 0; k < T; ++k)
-                if (n[k] > 0 && a.p == p[k] && a.n == n[k])
-                    j = k;
-            CHECK(j >= 0 && !g_single_vec[i], "single launch matches no tensor or is not elementwise");
+            int r = -1;
+            for (int k = 0; k < runs; ++k)
+                if (a.p == p[run_first[k]] && a.n == run_n[k])
+                    r = k;
+            CHECK(r >= 0 && !g_single_vec[i], "single launch matches no run or is not elementwise");
             CHECK(a.s_dev == reinterpret_cast<const disdp::StepScalars *>(sc),
                   "single launch step constants");
-            if (j >= 0)
-                ++seen[j];
+            if (r >= 0)
+                ++seen[r];
         }
-        for (int j = 0; j < T; ++j)
-            CHECK(seen[j] == (n[j] > 0 ? 1 : 0), "tensor %d launched %d times (n %lld)", j, seen[j],
-                  (long long)n[j]);
+        for (int r = 0; r < runs; ++r)
+            CHECK(seen[r] == 1, "run of tensor %d launched %d times (n %lld)", run_first[r], seen[r],
+                  (long long)run_n[r]);
 
         // one injected error
         int j0 = -1;

@@ -1,7 +1,7 @@
 """Lists of tensors around the sizes where a many-tensor call packs its
 launches differently: tensors that follow one another (one tensor to the
-kernels), slices of flat buffers (up to 240 to a launch, found in steps of
-16), buffers of their own (rows of W + 4 pointers), and the smallest tensors,
+kernels), slices of flat buffers (232 to a launch at W = 8, found in steps of
+16), buffers of their own (36 rows of W + 4 pointers), and the smallest tensors,
 which may have no whole group of four elements.  Every bit against the oracle
 on the flat arrays, and nothing written between the tensors.
 """
@@ -31,7 +31,8 @@ def _sizes(T, seed):
     (2, 8, "f32", "fp32", 0), (15, 1, "f32", "fp32", 1), (16, 8, "f32", "fp32", 37),
     (17, 4, "bf16", "fp32", 2), (239, 2, "f32", "fixed", 0), (240, 8, "bf16", "fixed", 6),
     (241, 1, "bf16", "fp32", 0), (500, 13, "f32", "fp32", 3), (70, 64, "bf16", "fp32", 0),
-    (40, 16, "f32", "fp32", 255)])
+    (40, 16, "f32", "fp32", 255), (36, 8, "bf16", "fp32", 4), (37, 8, "f32", "fixed", 9),
+    (232, 8, "f32", "fp32", 4), (233, 8, "bf16", "fp32", 0)])
 def test_packed_launches_match_oracle(pad, T, W, gdtype, mode, off):
     import paper_2409_00918_amd as dd
     sizes = _sizes(T, T)
