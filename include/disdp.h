@@ -62,8 +62,8 @@
  *             elements past a 4-element boundary (16 bytes for 4-byte
  *             arrays, 8 for bf16), e.g. any sub-range of aligned arrays: the
  *             first few elements (up to 255, reaching a common 256- or
- *             64-element boundary when the arrays agree that far) are done
- *             beside the rest.
+ *             64-element boundary when the arrays agree that far and are
+ *             that long) are done beside the rest.
  *             Arrays with unrelated offsets take them too when every array
  *             is aligned to its element size and the bf16 arrays can reach
  *             4-byte boundaries together: the first output is brought to a
