@@ -268,7 +268,9 @@ __device__ __forceinline__ float div_mid(float n, float d)
 // us that way, 219 this way, 215 with none far (the general form for
 // all, at the occupancy it likes: 218).  Zeros in the short form cost 24
 // instructions: 215 us with 0, 5% or 100% of the elements at zero, against 214
-// and 219 (5%).
+// and 219 (5%); 1% on a call over 1M elements.  (Looking for zeros only after the
+// check without them failed saved half of that 1% and cost waves with far
+// moments 2-4%.)
 __device__ __forceinline__ void adamw4(const StepScalars &s, const Reciprocals &r,
                                        const float (&agg)[4], float (&p)[4], float (&m)[4],
                                        float (&v)[4])
@@ -974,7 +976,8 @@ constexpr int aggregate_waves(int lane_bytes, bool bf16, bool converts_bf16)
 // 5, 4: 0.7, 0.7, 3.8, 4.3.  Converting: W = 9, 15 8: 3.3, 1.4; W = 19, 23, 24, 31, 63 7,
 // 7, 5, 7, 6: 1.6, 1.4, 2.1, 0.7, 2.6.
 // The aggregation alone, bf16: W = 9, 15 16: 0.6, 0.5; W = 17, 20, 23 12, 12, 14: 1.1,
-// 2.1, 0.2; W = 24, 31, 33, 39, 64 9, 13, 10, 11, 9: 1.1, 1.5, 0.9, 0.5, 2.4; fp32: W = 9,
+// 2.1, 0.2; W = 24, 31, 32, 33, 39, 64 9, 13, 8, 10, 11, 8: 1.1, 1.5, 3.4, 0.9, 0.5,
+// 1.4 (W = 32, 48, 64 at n = 1e7 to 1e8 8: 0.4% ahead of 9 on average); fp32: W = 9,
 // 15 9: 1.5, 1.5; W = 17, 23 7: 1.0, 2.6; W = 24, 31 6: 2.4, 1.1; W = 32, 64 5: 1.1, 1.7.
 int runtime_w_waves(int W, int gt, int mode, bool adam)
 {
@@ -984,7 +987,9 @@ int runtime_w_waves(int W, int gt, int mode, bool adam)
         if (W < 16)
             return adam ? 9 + __builtin_popcount(W) : 16;
         if (!adam)
-            return (pieces == 0 ? 9 : W >= 32 ? 9 + (pieces + 1) / 2 : 10 + pieces + (W < 24)) +
+            return (pieces == 0 ? 9 - (W >= 32)
+                    : W >= 32   ? 9 + (pieces + 1) / 2
+                                : 10 + pieces + (W < 24)) +
                    2 * converts;
         if (W >= 32 || pieces == 0)
             return 7 + (pieces + 1) / 2 + 2 * converts;
@@ -1230,11 +1235,12 @@ bool same_channels(const LaunchArgs &a)
 // aggregation of 16 at n = 1e7, -5%, at 22, n = 1.3e7, 4% ahead), fp32 too (W =
 // 1, 4, 8: -1%, -1%, -2%).  Above 7e8 elements it pays on one slab and loses on
 // allocations of their own: W = 16 at 8e8 0 and -10%, 1e9 +2 and -3%, 2e9 -2 and
-// -1%; W = 12 -9% at 8e8, W = 32 -7% at 1.25e9; at 6e8 it gains 1-4% on both.  It also loses when the arrays lie a multiple of 64
-// MiB apart, where the same tile of every array falls to the same channels:
-// fused W = 16, arrays 128 and 256 pages of 2 MiB apart 5.2 / 6.2 and 5.1 /
-// 6.3, 127 and 129 pages 5.4 / 6.2 and 4.9 / 6.2, 32 pages 6.2 / 6.3 (4 and
-// 8 tiles together did not do better over the layouts).
+// -1%; W = 12 -9% at 8e8, W = 32 -7% at 1.25e9; at 6e8 it gains 1-4% on both.
+// It also loses when the arrays lie a multiple of 64 MiB apart, where the same
+// tile of every array falls to the same channels: fused W = 16, arrays 128 and
+// 256 pages of 2 MiB apart 5.2 / 6.2 and 5.1 / 6.3, 127 and 129 pages 5.4 / 6.2
+// and 4.9 / 6.2, 32 pages 6.2 / 6.3 (4 and 8 tiles together did not do better
+// over the layouts).
 int tiles_together(const LaunchArgs &a, bool adam, int base_waves)
 {
     constexpr int kRounds = 20;
