@@ -191,9 +191,8 @@ __device__ __forceinline__ void adamw(const StepScalars &s, float agg, float &p,
 // What a lane derives from the step constants while its loads are in
 // flight, for the short forms of the two divisions by a bias correction c:
 // zh = 1/c correctly rounded and zl = 1/c - zh.  `tame`: the constants lie
-// where those forms hold (see adamw4).  `zero_v`: the distance of a second
-// moment of zero from the range they hold in: 0 when eps alone can be the
-// divisor.
+// where those forms hold (see adamw4).  `zero_v`: 1 when a second moment of
+// zero is among them, that is when eps alone can be the divisor, else 0.
 struct Reciprocals {
     float zh1, zl1, zh2, zl2;
     uint32_t zero_v;
@@ -212,7 +211,7 @@ __device__ __forceinline__ Reciprocals reciprocals(const StepScalars &s)
     // as integers (scalar compares): a sign bit or a NaN is above the ends
     constexpr uint32_t kLo = (127u - 24u) << 23, kOne = 127u << 23;
     constexpr uint32_t kEpsLo = (127u - 48u) << 23, kEps = (127u + 40u) << 23;
-    r.zero_v = __float_as_uint(s.eps) >= kEpsLo ? 0 : ~0u;
+    r.zero_v = __float_as_uint(s.eps) >= kEpsLo ? 1 : 0;
     r.tame = __float_as_uint(s.bc1) - kLo <= kOne - kLo &&
              __float_as_uint(s.bc2) - kLo <= kOne - kLo && __float_as_uint(s.eps) <= kEps;
     return r;
@@ -255,7 +254,7 @@ __device__ __forceinline__ float div_mid(float n, float d)
 }
 
 // adamw on the four elements of a lane, the same bits in fewer instructions
-// (a W = 8 fp32 group 316 -> 239 vector instructions, 30 of them while its
+// (a W = 8 fp32 group 316 -> 230 vector instructions, 30 of them while its
 // loads are in flight).
 // The kernel is bound by memory at shard sizes, but a launch of a few
 // megabytes runs its waves in step -- all load, all compute, all store -- and
@@ -266,7 +265,7 @@ __device__ __forceinline__ float div_mid(float n, float d)
 // takes the general form whole.  A branch per lane would run both forms in
 // such a wave: with 5% of the elements far, W = 8 fp32 at n = 2.5e7 took 237-242
 // us that way, 219 this way, 215 with none far (the general form for
-// all, at the occupancy it likes: 218).  Zeros in the short form cost 24
+// all, at the occupancy it likes: 218).  Zeros in the short form cost 15
 // instructions: 215 us with 0, 5% or 100% of the elements at zero, against 214
 // and 219 (5%); 1% on a call over 1M elements.  (Looking for zeros only after the
 // check without them failed saved half of that 1% and cost waves with far
@@ -278,19 +277,23 @@ __device__ __forceinline__ void adamw4(const StepScalars &s, const Reciprocals &
     constexpr uint32_t kMLo = (127u - 60u) << 23, kMHi = (127u + 20u) << 23;
     constexpr uint32_t kVLo = (127u - 96u) << 23, kVHi = (127u + 60u) << 23;
     float mi[4], vi[4];
-    uint32_t far_m = 0, far_v = 0;   // largest distance above the lower ends (wraps below them)
+    // Ends of the moments' bits: of m with the sign below them, so that -0 is 1.
+    // One less, +0 is above every lower end.
+    uint32_t lo_m = ~0u, hi_m = 0, lo_v = ~0u, hi_v = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const float g = agg[e] * s.grad_scale;
         mi[e] = s.b1 * m[e] + s.omb1 * g;
         vi[e] = s.b2 * v[e] + s.omb2 * (g * g);
-        const uint32_t um = __float_as_uint(mi[e]), uv = __float_as_uint(vi[e]);
-        const uint32_t dm = um ? (um << 1) - 2 * kMLo : 0;
-        const uint32_t dv = uv ? uv - kVLo : r.zero_v;
-        far_m = dm > far_m ? dm : far_m;
-        far_v = dv > far_v ? dv : far_v;
+        const uint32_t um = __builtin_rotateleft32(__float_as_uint(mi[e]), 1);
+        const uint32_t uv = __float_as_uint(vi[e]);
+        lo_m = um - 1 < lo_m ? um - 1 : lo_m;
+        hi_m = um > hi_m ? um : hi_m;
+        lo_v = uv - r.zero_v < lo_v ? uv - r.zero_v : lo_v;
+        hi_v = uv > hi_v ? uv : hi_v;
     }
-    const bool mid = r.tame && far_m <= 2 * (kMHi - kMLo) && far_v <= kVHi - kVLo;
+    const bool mid = r.tame && lo_m >= 2 * kMLo - 1 && hi_m <= 2 * kMHi + 1 &&
+                     lo_v >= kVLo - r.zero_v && hi_v <= kVHi;
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(!mid) == 0, 1)) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
